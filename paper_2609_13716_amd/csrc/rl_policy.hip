@@ -410,40 +410,41 @@ static bool try_launch_policy_reg(const PolicyArgs& pol, const void* obs, const 
 // ------------------------------------------------ tiled policy forward ----
 //
 // bf16 policy forward for wide layers (the 12x12 LBF, kitchen and Hanabi
-// policies), structured as three chained GEMMs per tile of BM rows:
-//   * 4 waves in a 2 x 2 grid over (output units, rows); each wave holds the
-//     fp32 accumulators of HMAX/2 units x BM/2 rows for a whole layer;
-//   * layer-1 weights and observations, and layer-2 weights, are staged
-//     through a ring of NB LDS buffers, one K slice of 32 at a time; every
-//     weight byte staged serves all BM rows of the tile.  With NB = 3 the
-//     global loads of slice s+3 are issued a full step before they are
-//     stored to LDS, and the MFMA operands of slice s+1 are read from LDS
-//     while the MFMAs of slice s run;
-//   * h1 stays in LDS; h2 overwrites it once layer 2 has read it;
-//   * layer 3 is computed transposed (actions x rows) from h2.
-// As in the register-resident kernels, every output is one MFMA chain over K
-// in increasing order, bias added after, so the logits are bit-identical to
-// the other policy paths.
-constexpr int PT_KC = 32;  // K slice per step: one bf16 MFMA K step
-constexpr int PT_NT = 256;
+// policies): three chained GEMMs per tile of BM = 16 MT rows, H / 64 waves.
+//   * Wave w computes hidden units 64 w .. 64 w + 63 of every row of the tile
+//     (4 x MT accumulator tiles), so each weight byte is read by one wave
+//     only: weights go from L2 straight into the MFMA operand registers (the
+//     fragment-major copy: 1 KB contiguous per load), two K steps ahead, and
+//     never through LDS.
+//   * Observation rows are staged through LDS in stages of 64 features (128
+//     contiguous bytes per row, 16-byte chunks XOR-swizzled by row), loaded
+//     one stage ahead into registers.
+//   * h1 stays in LDS (over the staging buffers); h2 overwrites it once every
+//     wave has read h1; layer 3 is computed transposed (actions x rows).
+// Every output is one MFMA chain over K in increasing order, bias added
+// after, so the logits are bit-identical to the other policy paths.
+//
+// What bounds it: at MT 8 a K step is 32 MFMAs per wave (512 cycles on its
+// SIMD) against 16 KB (256 units) of weights and 8 KB of rows into the CU and
+// 32 KB of LDS reads (256 cycles); under this load the clock falls to about
+// 1.9 GHz, and a layer's tanh epilogue (128 values per lane at about 34 cycles) is
+// hidden only as far as the two workgroups of a CU drift apart.  Tiles of 64 rows
+// with the weights staged through LDS moved 60 KB of LDS per 64-row K step
+// (480 cycles against 256 of MFMA): 1170-256-256-6 over 262144 rows 360 -> 224 us,
+// 658-512-512-20 over 100003 rows 328 -> 159 us, 432-256-256-6 over 262144 rows
+// 181 -> 102 us.  Loading the rows two stages ahead, or as single words, changed nothing.
+constexpr int PT_SK = 64;  // features per staged slice: two MFMA K steps
 
-template <int HMAX, int BM, int NB>
+template <int H, int MT>
 struct PtLayout {
-  static constexpr int LDH = HMAX + 8;  // pitch of the resident activation tile
+  static constexpr int BM = 16 * MT;
+  static constexpr int LDH = H + 8;  // pitch of the resident activation tile
   static constexpr size_t H_BYTES = (size_t)BM * LDH * 2;
-  static constexpr size_t W_BYTES = (size_t)HMAX * PT_KC * 2;  // one staged weight slice
-  static constexpr size_t X_BYTES = (size_t)BM * PT_KC * 2;    // one staged observation slice
-  static constexpr size_t OFF_W = H_BYTES;
-  static constexpr size_t OFF_X = OFF_W + NB * W_BYTES;
-  static constexpr size_t OFF_B = OFF_X + NB * X_BYTES;  // fp32 biases of layers 1 and 2
-  static constexpr size_t TOTAL = OFF_B + 2 * HMAX * 4;
+  static constexpr size_t X_BYTES = (size_t)BM * PT_SK * 2;  // one staged slice
+  static constexpr size_t OFF_B = H_BYTES;                   // fp32 biases of layers 1 and 2
+  static constexpr size_t TOTAL = OFF_B + 2 * H * 4;
+  static_assert(2 * X_BYTES <= H_BYTES, "both staging buffers lie in the activation tile");
 };
-
-// Element offset of 16-byte vector q (k = 8q..8q+7) of row n in a staged
-// slice: rows of 64 bytes, vectors XOR-swizzled by (n / 2) % 4 so that any 8
-// consecutive rows of an MFMA operand read fill the 32 LDS banks without
-// conflict.  The swizzle does not change when n moves by 16 (an operand tile).
-__device__ __forceinline__ int pt_slot(int n, int q) { return n * PT_KC + 8 * (q ^ ((n >> 1) & 3)); }
 
 // Buffer resource over `bytes` bytes at p (raw: loads past the end read 0).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pt_rsrc(const void* p, uint32_t bytes) {
@@ -461,268 +462,254 @@ __device__ __forceinline__ u32x4 pt_mask8(u32x4 v, int left) {
   return v;
 }
 
-template <int HMAX, int BM, int NB, int MINB, bool PK>
-__global__ __launch_bounds__(PT_NT, MINB) void policy_fwd_tiled_kernel(PolicyArgs pol, const uint16_t* __restrict__ obs,
-                                                                 const uint8_t* __restrict__ legal, int64_t rows,
-                                                                 float* __restrict__ logits) {
-  using L = PtLayout<HMAX, BM, NB>;
-  constexpr int UT = HMAX / 32;  // unit tiles of a wave (half the units)
-  constexpr int RT = BM / 32;    // row tiles of a wave (half the rows)
-  constexpr int HH = HMAX / 2;   // units of a wave
-  constexpr int WV = HMAX * 4 / PT_NT, XV = (BM * 4 + PT_NT - 1) / PT_NT;  // staged vectors per thread
-  static_assert(NB == 2 || NB == 3, "two or three slice buffers");
-  static_assert(HMAX * 4 % PT_NT == 0, "whole weight vectors per thread");
+template <int H, int MT, bool PK>
+__global__ __launch_bounds__(H, H == 256 ? 2 : 1) void policy_fwd_tiled_kernel(PolicyArgs pol,
+                                                                               const uint16_t* __restrict__ obs,
+                                                                               const uint8_t* __restrict__ legal,
+                                                                               int64_t rows, float* __restrict__ logits) {
+  using L = PtLayout<H, MT>;
+  constexpr int NT = H, NW = H / 64, BM = L::BM;
+  constexpr int UT = 4;  // unit tiles of a wave
+  constexpr int XV = (BM * 8 + NT - 1) / NT;  // staged 16-byte vectors per thread
+  constexpr bool XALL = BM * 8 % NT == 0;
   extern __shared__ __align__(16) uint8_t smem[];
   uint16_t* hs = reinterpret_cast<uint16_t*>(smem);
-  uint16_t* wst = reinterpret_cast<uint16_t*>(smem + L::OFF_W);
-  uint16_t* xst = reinterpret_cast<uint16_t*>(smem + L::OFF_X);
+  uint16_t* xst = hs;  // the two staging buffers, until layer 1's outputs are stored
   float* bias_s = reinterpret_cast<float*>(smem + L::OFF_B);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wu = wave & 1, wr = wave >> 1;
   const int D = pol.D, NA = pol.NA;
   const int64_t row0 = (int64_t)blockIdx.x * BM;
   const int nrow = (int)min((int64_t)BM, rows - row0);
-  const uint16_t* W3 = static_cast<const uint16_t*>(pol.W[2]);
 
-  for (int i = tid; i < 2 * HMAX; i += PT_NT)
-    bias_s[i] = bf16_to_f32(i < HMAX ? static_cast<const uint16_t*>(pol.b[0])[i]
-                                     : static_cast<const uint16_t*>(pol.b[1])[i - HMAX]);
+  for (int i = tid; i < 2 * H; i += NT)
+    bias_s[i] = bf16_to_f32(i < H ? static_cast<const uint16_t*>(pol.b[0])[i]
+                                  : static_cast<const uint16_t*>(pol.b[1])[i - H]);
 
-  // One dense tanh layer of HMAX units: out = tanh(in W^T + b) into hs.
-  // Layer 1 (tag true) stages observation rows with the weights; layer 2
-  // reads its input from hs.
-  auto layer = [&](auto l1_tag, const uint16_t* __restrict__ W, const uint16_t* __restrict__ Wp, int K,
-                   const float* bias) {
-    constexpr bool L1 = decltype(l1_tag)::value;
-    const int nsteps = (K + PT_KC - 1) / PT_KC;
-    // Weight slices are fetched one step before they are stored to LDS (they
-    // come from L2); observation slices, which come from HBM, PX steps
-    // before, through a ring of PX register slots (slot = slice % PX).
-    constexpr int PX = NB == 3 ? 4 : 1;
-    u32x4 wv[WV], xv[PX][XV];
-    // per-thread byte offsets of the staged vectors (global) and their LDS
-    // slots, fixed for the layer; the slice offset goes in a scalar register
-    // PK: weights from the fragment-major copy (1 KB per 16 rows x 32 k),
-    // one contiguous 1 KB block per wave-wide load instead of 16 rows x 64 B
-    const int S = (K + PT_KC - 1) / PT_KC;
-    const __amdgpu_buffer_rsrc_t wres =
-        PK ? pt_rsrc(Wp, (uint32_t)(HMAX / 16) * S * 1024) : pt_rsrc(W, (uint32_t)HMAX * K * 2);
-    const __amdgpu_buffer_rsrc_t xres = pt_rsrc(obs + (size_t)row0 * D, (uint32_t)nrow * D * 2);
-    int wgo[WV], wlo[WV], xgo[XV], xlo[XV];
+  // weight operands of a layer: unit tile 4 wave + u, K step st
+  auto w_rsrc = [&](int l, int K) {
+    const int S = (K + 31) / 32;
+    return PK ? pt_rsrc(pol.Wp[l], (uint32_t)(H / 16) * S * 1024) : pt_rsrc(pol.W[l], (uint32_t)H * K * 2);
+  };
+  auto w_offs = [&](int K, int (&wo)[UT]) {
+    const int S = (K + 31) / 32;
 #pragma unroll
-    for (int j = 0; j < WV; ++j) {
-      const int v = tid + j * PT_NT;
-      if constexpr (PK) {
-        const int t = v >> 6, l = v & 63;  // operand block of tile t, lane l: row 16t + l % 16, chunk l / 16
-        wgo[j] = (t * S * 64 + l) * 16;
-        wlo[j] = pt_slot(16 * t + (l & 15), l >> 4);
-      } else {
-        const int n = v >> 2, q = v & 3;
-        wgo[j] = (n * K + 8 * q) * 2;
-        wlo[j] = pt_slot(n, q);
-      }
-    }
+    for (int u = 0; u < UT; ++u)
+      wo[u] = PK ? ((4 * wave + u) * S * 64 + lane) * 16 : ((64 * wave + 16 * u + (lane & 15)) * K + 8 * (lane >> 4)) * 2;
+  };
+  auto w_load = [&](__amdgpu_buffer_rsrc_t r, int off, int st) -> u32x4 {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, st * (PK ? 1024 : 64), 0);
+  };
+
+  f32x4 acc[UT][MT];
+  auto clear = [&]() {
 #pragma unroll
-    for (int j = 0; j < XV; ++j) {
-      const int v = tid + j * PT_NT, r = v >> 2, q = v & 3;
-      xgo[j] = (r * D + 8 * q) * 2;  // rows past nrow lie past the resource: read as 0
-      xlo[j] = pt_slot(r, q);
-    }
-    constexpr bool XALL = BM * 4 % PT_NT == 0;  // every thread stages XV observation vectors
-    auto fetch_w = [&](int st) {
+    for (int u = 0; u < UT; ++u)
 #pragma unroll
-      for (int j = 0; j < WV; ++j)
-        wv[j] = __builtin_amdgcn_raw_buffer_load_b128(wres, wgo[j], PK ? st * 1024 : st * PT_KC * 2, 0);
-    };
-    auto fetch_x = [&](int st, u32x4 (&x)[XV]) {
-      if constexpr (L1) {
+      for (int m = 0; m < MT; ++m) acc[u][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // tanh(acc + bias) to the activation tile: four consecutive units of one row per lane
+  auto epilogue = [&](const float* bias) {
 #pragma unroll
-        for (int j = 0; j < XV; ++j)
-          if (XALL || tid + j * PT_NT < BM * 4)
-            x[j] = __builtin_amdgcn_raw_buffer_load_b128(xres, xgo[j], st * PT_KC * 2, 0);
-      }
-    };
-    // store slice st to LDS buffer st % NB, zeroing what lies past K in the
-    // partial last slice (uniform branch; q = tid % 4 for every vector)
-    auto stage = [&](int st, u32x4 (&x)[XV]) {
-      const int k0 = st * PT_KC;
-      const bool part = k0 + PT_KC > K;
-      const int left = K - k0 - 8 * (tid & 3);
-      uint16_t* wb = wst + (st % NB) * (HMAX * PT_KC);
-#pragma unroll
-      for (int j = 0; j < WV; ++j)  // (the packed copy already holds zeros past K)
-        *reinterpret_cast<u32x4*>(wb + wlo[j]) = (part && !PK) ? pt_mask8(wv[j], left) : wv[j];
-      if constexpr (L1) {
-        uint16_t* xb = xst + (st % NB) * (BM * PT_KC);
-#pragma unroll
-        for (int j = 0; j < XV; ++j)
-          if (XALL || tid + j * PT_NT < BM * 4)
-            *reinterpret_cast<u32x4*>(xb + xlo[j]) = part ? pt_mask8(x[j], left) : x[j];
-      }
-    };
-    // MFMA operands of slice st (staged in buffer st % NB): unit tiles of W
-    // and row tiles of the input, at fixed offsets from one lane base each
-    const int a_lo = pt_slot(wu * HH + (lane & 15), lane >> 4);
-    const int b_lo = L1 ? pt_slot(wr * (BM / 2) + (lane & 15), lane >> 4)
-                        : (wr * (BM / 2) + (lane & 15)) * L::LDH + 8 * (lane >> 4);
-    auto frags = [&](int st, u32x4 (&a)[UT], u32x4 (&b)[RT]) {
-      const uint16_t* wb = wst + (st % NB) * (HMAX * PT_KC) + a_lo;
-#pragma unroll
-      for (int ut = 0; ut < UT; ++ut) a[ut] = *reinterpret_cast<const u32x4*>(wb + ut * 16 * PT_KC);
-      if constexpr (L1) {
-        const uint16_t* xb = xst + (st % NB) * (BM * PT_KC) + b_lo;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) b[rt] = *reinterpret_cast<const u32x4*>(xb + rt * 16 * PT_KC);
-      } else {
-        const uint16_t* hb = hs + b_lo + st * PT_KC;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) b[rt] = *reinterpret_cast<const u32x4*>(hb + rt * 16 * L::LDH);
-      }
-    };
-    f32x4 acc[UT][RT];
-#pragma unroll
-    for (int ut = 0; ut < UT; ++ut)
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) acc[ut][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto mma = [&](const u32x4 (&a)[UT], const u32x4 (&b)[RT]) {
-#pragma unroll
-      for (int ut = 0; ut < UT; ++ut)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc[ut][rt] = mfma16<DT_BF16>(a[ut], b[rt], acc[ut][rt]);
-    };
-    if constexpr (NB == 3) {
-      // prologue: slices 0 and 1 in LDS, weights of slice 2 and observations
-      // of slices 2 .. PX+1 in flight
-      fetch_w(0);
-      fetch_x(0, xv[0]);
-      stage(0, xv[0]);
-      if (1 < nsteps) {
-        fetch_w(1);
-        fetch_x(1, xv[1]);
-        stage(1, xv[1]);
-      }
-      if (2 < nsteps) fetch_w(2);
-#pragma unroll
-      for (int u = 2; u < PX + 2; ++u)
-        if (u < nsteps) fetch_x(u, xv[u % PX]);
-      __syncthreads();
-      u32x4 a0[UT], b0[RT], a1[UT], b1[RT];
-      frags(0, a0, b0);
-      // one step (U = st % PX): store slice st+2 (its buffer was last read at
-      // step st-1), fetch the weights of slice st+3 and the observations of
-      // slice st+2+PX into the slot just stored, read slice st+1's operands,
-      // then run slice st's MFMAs, behind which these memory operations land
-      auto step = [&](auto u_tag, int st, const u32x4 (&a)[UT], const u32x4 (&b)[RT], u32x4 (&an)[UT],
-                      u32x4 (&bn)[RT]) {
-        constexpr int U = decltype(u_tag)::value;
-        if (st + 2 < nsteps) stage(st + 2, xv[(U + 2) % PX]);
-        if (st + 3 < nsteps) fetch_w(st + 3);
-        if (st + 2 + PX < nsteps) fetch_x(st + 2 + PX, xv[(U + 2) % PX]);
-        if (st + 1 < nsteps) frags(st + 1, an, bn);
-        mma(a, b);
-        __syncthreads();
-      };
-      static_assert(PX % 2 == 0, "operand registers alternate within the unrolled steps");
-      for (int st = 0; st < nsteps; st += 4) {
-        step(std::integral_constant<int, 0>{}, st, a0, b0, a1, b1);
-        if (st + 1 < nsteps) step(std::integral_constant<int, 1>{}, st + 1, a1, b1, a0, b0);
-        if (st + 2 < nsteps) step(std::integral_constant<int, 2>{}, st + 2, a0, b0, a1, b1);
-        if (st + 3 < nsteps) step(std::integral_constant<int, 3>{}, st + 3, a1, b1, a0, b0);
-      }
-    } else {
-      fetch_w(0);
-      fetch_x(0, xv[0]);
-      stage(0, xv[0]);
-      __syncthreads();
-      for (int st = 0; st < nsteps; ++st) {
-        if (st + 1 < nsteps) {
-          fetch_w(st + 1);
-          fetch_x(st + 1, xv[0]);
-        }
-        u32x4 a[UT], b[RT];
-        frags(st, a, b);
-        mma(a, b);
-        if (st + 1 < nsteps) stage(st + 1, xv[0]);
-        __syncthreads();
-      }
-    }
-    // every wave is past its last read of hs (layer 2 input): overwrite it
-#pragma unroll
-    for (int ut = 0; ut < UT; ++ut) {
-      const int u0 = wu * HH + ut * 16 + 4 * (lane >> 4);
+    for (int u = 0; u < UT; ++u) {
+      const int u0 = 64 * wave + 16 * u + 4 * (lane >> 4);
       const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + u0);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const int r = wr * (BM / 2) + rt * 16 + (lane & 15);
+      for (int m = 0; m < MT; ++m) {
         float v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = fast_tanh(acc[ut][rt][q] + b4[q]);
-        const uint32_t lo = pack_bf16x2(v[0], v[1]);
-        const uint32_t hi = pack_bf16x2(v[2], v[3]);
+        for (int q = 0; q < 4; ++q) v[q] = fast_tanh(acc[u][m][q] + b4[q]);
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<u32x2*>(hs + r * L::LDH + u0) = u32x2{lo, hi};
+        *reinterpret_cast<u32x2*>(hs + (16 * m + (lane & 15)) * L::LDH + u0) =
+            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
       }
     }
-    __syncthreads();
   };
-  layer(std::true_type{}, static_cast<const uint16_t*>(pol.W[0]), static_cast<const uint16_t*>(pol.Wp[0]), D, bias_s);
-  layer(std::false_type{}, static_cast<const uint16_t*>(pol.W[1]), static_cast<const uint16_t*>(pol.Wp[1]), HMAX,
-        bias_s + HMAX);
 
-  // layer 3, transposed: logits^T = W3 h2^T, items (action tile, row tile)
-  constexpr int K3 = HMAX / PT_KC;
+  u32x4 wr[2][UT];  // weight operands of K steps st, st + 1 (slot = st % 2), each refilled in place for st + 2
+  // ---- layer 1 ----
+  {
+    const int S = (D + 31) / 32, NS = (D + PT_SK - 1) / PT_SK;
+    const __amdgpu_buffer_rsrc_t wres = w_rsrc(0, D);
+    const __amdgpu_buffer_rsrc_t xres = pt_rsrc(obs + (size_t)row0 * D, (uint32_t)nrow * D * 2);
+    int wo[UT], xgo[XV], xlo[XV];
+    w_offs(D, wo);
+#pragma unroll
+    for (int j = 0; j < XV; ++j) {
+      const int v = tid + j * NT, r = v >> 3, c = v & 7;
+      xgo[j] = (r * D + 8 * c) * 2;  // rows past nrow lie past the resource: read as 0
+      xlo[j] = r * PT_SK + 8 * (c ^ (r & 7));
+    }
+    u32x4 xv[XV];
+    auto fetch_x = [&](int s) {
+#pragma unroll
+      for (int j = 0; j < XV; ++j)
+        if (XALL || tid + j * NT < BM * 8) xv[j] = __builtin_amdgcn_raw_buffer_load_b128(xres, xgo[j], s * PT_SK * 2, 0);
+    };
+    auto store_x = [&](int s) {
+      uint16_t* xb = xst + (s & 1) * (BM * PT_SK);
+#pragma unroll
+      for (int j = 0; j < XV; ++j)
+        if (XALL || tid + j * NT < BM * 8) *reinterpret_cast<u32x4*>(xb + xlo[j]) = xv[j];
+    };
+    const int brow = (lane & 15) * PT_SK;
+    // K step st = 2 s + KK of staged slice s
+    auto step = [&](auto kk_c, int s) {
+      constexpr int KK = decltype(kk_c)::value;
+      const int st = 2 * s + KK;
+      const uint16_t* xb = xst + (s & 1) * (BM * PT_SK) + brow + 8 * ((4 * KK + (lane >> 4)) ^ (lane & 7));
+      u32x4 b[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) b[m] = *reinterpret_cast<const u32x4*>(xb + m * 16 * PT_SK);
+      if (st * 32 + 32 > D) {  // the partial last K step: nothing past the row takes part (uniform branch)
+        const int left = D - st * 32 - 8 * (lane >> 4);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) b[m] = pt_mask8(b[m], left);
+        if constexpr (!PK) {
+#pragma unroll
+          for (int u = 0; u < UT; ++u) wr[KK][u] = pt_mask8(wr[KK][u], left);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UT; ++u) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(wr[KK][u], b[m], acc[u][m]);
+        wr[KK][u] = w_load(wres, wo[u], st + 2);  // (past the last step: unused)
+      }
+    };
+    fetch_x(0);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int u = 0; u < UT; ++u) wr[kk][u] = w_load(wres, wo[u], kk);
+    clear();
+    store_x(0);
+    if (NS > 1) fetch_x(1);
+    __syncthreads();
+    for (int s = 0; s < NS; ++s) {
+      step(std::integral_constant<int, 0>{}, s);
+      if (2 * s + 1 < S) step(std::integral_constant<int, 1>{}, s);
+      if (s + 1 < NS) store_x(s + 1);  // (its buffer was last read in stage s - 1)
+      if (s + 2 < NS) fetch_x(s + 2);
+      __syncthreads();
+    }
+  }
+  // ---- layer 2: its first weights are on their way during layer 1's epilogue ----
+  {
+    const __amdgpu_buffer_rsrc_t wres = w_rsrc(1, H);
+    int wo[UT];
+    w_offs(H, wo);
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int u = 0; u < UT; ++u) wr[kk][u] = w_load(wres, wo[u], kk);
+    epilogue(bias_s);
+    clear();
+    __syncthreads();
+    const uint16_t* hb = hs + (lane & 15) * L::LDH + 8 * (lane >> 4);
+#pragma unroll 2
+    for (int st = 0; st < H / 32; st += 2) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        u32x4 b[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) b[m] = *reinterpret_cast<const u32x4*>(hb + m * 16 * L::LDH + (st + kk) * 32);
+#pragma unroll
+        for (int u = 0; u < UT; ++u) {
+#pragma unroll
+          for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(wr[kk][u], b[m], acc[u][m]);
+          wr[kk][u] = w_load(wres, wo[u], st + kk + 2);
+        }
+      }
+    }
+  }
+  __syncthreads();  // every wave is past its last read of h1
+  epilogue(bias_s + H);
+  __syncthreads();
+
+  // ---- layer 3, transposed: logits^T = W3 h2^T, wave w takes row tiles w, w + NW, ... ----
+  constexpr int K3 = H / 32;
   const int nat = (NA + 15) >> 4;
-  for (int item = wave; item < nat * (BM / 16); item += PT_NT / 64) {
-    const int mt = item % nat, rt = item / nat;
+  for (int mt = 0; mt < nat; ++mt) {
     const int a_row = mt * 16 + (lane & 15);
-    const uint16_t* w3r = W3 + (size_t)(a_row < NA ? a_row : 0) * HMAX + 8 * (lane >> 4);
-    const int r = rt * 16 + (lane & 15);
-    u32x4 a3[K3];
+    const uint16_t* w3r = static_cast<const uint16_t*>(pol.W[2]) + (size_t)(a_row < NA ? a_row : 0) * H + 8 * (lane >> 4);
+    for (int rt = wave; rt < MT; rt += NW) {
+      const int r = rt * 16 + (lane & 15);
+      u32x4 a3[K3];
 #pragma unroll
-    for (int ks = 0; ks < K3; ++ks)
-      a3[ks] = a_row < NA ? *reinterpret_cast<const u32x4*>(w3r + ks * PT_KC) : u32x4{0u, 0u, 0u, 0u};
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int ks = 0; ks < K3; ++ks)
+        a3[ks] = a_row < NA ? *reinterpret_cast<const u32x4*>(w3r + ks * 32) : u32x4{0u, 0u, 0u, 0u};
+      f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < K3; ++ks)
-      acc = mfma16<DT_BF16>(a3[ks], *reinterpret_cast<const u32x4*>(hs + r * L::LDH + ks * PT_KC + 8 * (lane >> 4)),
-                            acc);
-    if (r < nrow) {
+      for (int ks = 0; ks < K3; ++ks)
+        c = mfma16<DT_BF16>(a3[ks], *reinterpret_cast<const u32x4*>(hs + r * L::LDH + ks * 32 + 8 * (lane >> 4)), c);
+      if (r < nrow) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int act = mt * 16 + 4 * (lane >> 4) + q;
-        if (act < NA) {
-          const size_t gi = (size_t)(row0 + r) * NA + act;
-          const float lg = acc[q] + bf16_to_f32(static_cast<const uint16_t*>(pol.b[2])[act]);
-          logits[gi] = (legal == nullptr || legal[gi] != 0) ? lg : -INFINITY;
+        for (int q = 0; q < 4; ++q) {
+          const int act = mt * 16 + 4 * (lane >> 4) + q;
+          if (act < NA) {
+            const size_t gi = (size_t)(row0 + r) * NA + act;
+            const float lg = c[q] + bf16_to_f32(static_cast<const uint16_t*>(pol.b[2])[act]);
+            logits[gi] = (legal == nullptr || legal[gi] != 0) ? lg : -INFINITY;
+          }
         }
       }
     }
   }
 }
 
-template <int HMAX, int BM, int NB, int MINB, bool PK>
-static hipError_t launch_policy_tiled_pk(const PolicyArgs& pol, const void* obs, const uint8_t* legal, int64_t rows,
+template <int H, int MT, bool PK>
+static hipError_t launch_policy_tiled_mt(const PolicyArgs& pol, const void* obs, const uint8_t* legal, int64_t rows,
                                          float* logits, hipStream_t s) {
-  using L = PtLayout<HMAX, BM, NB>;
+  using L = PtLayout<H, MT>;
   static_assert(L::TOTAL <= MAX_LDS_BYTES, "tile fits in LDS");
   static bool attr = false;
   if (!attr) {
-    const hipError_t e = hipFuncSetAttribute((const void*)policy_fwd_tiled_kernel<HMAX, BM, NB, MINB, PK>,
+    const hipError_t e = hipFuncSetAttribute((const void*)policy_fwd_tiled_kernel<H, MT, PK>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)L::TOTAL);
     if (e != hipSuccess) return e;
     attr = true;
   }
-  const unsigned grid = (unsigned)((rows + BM - 1) / BM);
-  policy_fwd_tiled_kernel<HMAX, BM, NB, MINB, PK><<<dim3(grid), PT_NT, L::TOTAL, s>>>(
-      pol, static_cast<const uint16_t*>(obs), legal, rows, logits);
+  const unsigned grid = (unsigned)((rows + L::BM - 1) / L::BM);
+  policy_fwd_tiled_kernel<H, MT, PK><<<dim3(grid), H, L::TOTAL, s>>>(pol, static_cast<const uint16_t*>(obs), legal,
+                                                                     rows, logits);
   return hipGetLastError();
 }
 
-template <int HMAX, int BM, int NB, int MINB>
+// Row tiles of a workgroup.  A CU works through ceil(workgroups / 256)
+// workgroups, and a workgroup of MT row tiles costs about k + MT: the weights
+// it reads and its prologue are the constant part (k = 3 at 256 units, two workgroups
+// sharing the CU; 2 at 512).  The least product is taken, the larger tile on
+// ties.  Measured over MT 1, 2, 4, 5, 6, 7, 8 (us; chosen one starred):
+// 1170-256-256-6 at 262144 rows 648, 415, 269, 264, 250, 243, 224*; at 16384
+// rows 35, 22.7, 23.3*, 26, 27, 31, 33; at 4096 rows 13.0*, 13.0, 17, 21, 23, 27, 28;
+// 658-512-512-20 at 100003 rows 317, 189, 169, 159*, 175, 156, 173; at 98304
+// rows 345, 188, 154, 159, 145, 156, 135*.
+static int pt_pick_mt(int H, int64_t rows) {
+  const int k = H == 256 ? 3 : 2;
+  int best = 8;
+  int64_t best_cost = INT64_MAX;
+  for (int mt : {8, 7, 6, 5, 4, 2, 1}) {
+    const int64_t wgs = (rows + 16 * mt - 1) / (16 * mt), cost = (wgs + 255) / 256 * (k + mt);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = mt;
+    }
+  }
+  return best;
+}
+
+template <int H, bool PK>
 static hipError_t launch_policy_tiled(const PolicyArgs& pol, const void* obs, const uint8_t* legal, int64_t rows,
                                       float* logits, hipStream_t s) {
-  return pol.Wp[0] != nullptr ? launch_policy_tiled_pk<HMAX, BM, NB, MINB, true>(pol, obs, legal, rows, logits, s)
-                              : launch_policy_tiled_pk<HMAX, BM, NB, MINB, false>(pol, obs, legal, rows, logits, s);
+  switch (pt_pick_mt(H, rows)) {
+    case 1: return launch_policy_tiled_mt<H, 1, PK>(pol, obs, legal, rows, logits, s);
+    case 2: return launch_policy_tiled_mt<H, 2, PK>(pol, obs, legal, rows, logits, s);
+    case 4: return launch_policy_tiled_mt<H, 4, PK>(pol, obs, legal, rows, logits, s);
+    case 5: return launch_policy_tiled_mt<H, 5, PK>(pol, obs, legal, rows, logits, s);
+    case 6: return launch_policy_tiled_mt<H, 6, PK>(pol, obs, legal, rows, logits, s);
+    case 7: return launch_policy_tiled_mt<H, 7, PK>(pol, obs, legal, rows, logits, s);
+    default: return launch_policy_tiled_mt<H, 8, PK>(pol, obs, legal, rows, logits, s);
+  }
 }
 
 // Shapes the tiled kernel serves: bf16, two hidden layers of 256 or of 512
@@ -730,10 +717,13 @@ static hipError_t launch_policy_tiled(const PolicyArgs& pol, const void* obs, co
 static bool try_launch_policy_tiled(const PolicyArgs& pol, const void* obs, const uint8_t* legal, int64_t rows,
                                     float* logits, hipStream_t s, hipError_t* err) {
   if (pol.dt != DT_BF16 || pol.D % 2 != 0 || pol.H1 != pol.H2 || pol.NA > MAX_NA) return false;
+  const bool pk = pol.Wp[0] != nullptr;
   if (pol.H1 == 256)
-    *err = launch_policy_tiled<256, 64, 2, 2>(pol, obs, legal, rows, logits, s);  // two workgroups per CU
+    *err = pk ? launch_policy_tiled<256, true>(pol, obs, legal, rows, logits, s)
+              : launch_policy_tiled<256, false>(pol, obs, legal, rows, logits, s);
   else if (pol.H1 == 512)
-    *err = launch_policy_tiled<512, 64, 2, 1>(pol, obs, legal, rows, logits, s);
+    *err = pk ? launch_policy_tiled<512, true>(pol, obs, legal, rows, logits, s)
+              : launch_policy_tiled<512, false>(pol, obs, legal, rows, logits, s);
   else
     return false;
   return true;

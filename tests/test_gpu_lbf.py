@@ -493,3 +493,35 @@ def test_rollout_run_7x7_constant_levels(dtype):
     assert states == ref["states"]
     assert all(s.agent_level == [1, 1] and s.food_level == [2, 2, 2] for s in states)
     assert ref["done"].any()
+
+
+@pytest.mark.parametrize("dims", [(34, 256, 256, 6), (278, 256, 256, 16), (70, 512, 512, 20), (26, 512, 512, 6)])
+@pytest.mark.parametrize("pack", [True, False])
+def test_policy_forward_tile_sizes(dims, pack):
+    """Wide policies take 16 to 128 rows per workgroup by the batch size: batches that select each tile size,
+    ragged, give the same logits, bit for bit, for the rows they share, and they stay within the bf16
+    tolerance of float32 sums.  The partial K step takes nothing past its row: the row before one of NaNs, and
+    the last row of a batch that NaNs follow in memory, are finite."""
+    require_gpu()
+    _note(f"policy_forward tile sizes {dims} pack={pack}")
+    ws, bs = workloads.policy_weights(dims, seed=29, bias_scale=0.3)
+    pol = R.Policy(ws, bs, "bf16", pack=pack)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    most = 2 * 256 * 128 + 9
+    buf = torch.randint(0, 3, (most + 64, dims[0]), generator=g, device="cuda").to(torch.bfloat16)
+    buf[most:] = float("nan")
+    full = R.policy_forward(pol, buf[:most])
+    x = buf[:most].float()
+    for l in range(3):
+        x = x @ pol.W[l].float().T + pol.b[l].float()
+        if l < 2:
+            x = torch.tanh(x).to(torch.bfloat16).float()
+    assert_logits_close(full.cpu().numpy(), x.cpu().numpy(), RTOL["bf16"])
+    for rows in (1, 17, 4097, 8193, 16385, 20481, 24577, 28673, 32769, 50001):
+        part = buf[:rows].clone()
+        assert torch.equal(R.policy_forward(pol, part), full[:rows]), rows
+    nan = buf[:40].clone()
+    nan[1::2] = float("nan")
+    got = R.policy_forward(pol, nan)
+    assert torch.equal(got[0::2], full[:40:2]) and bool(torch.isnan(got[1::2]).all())
