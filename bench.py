@@ -542,12 +542,12 @@ PHASE_CASES = (
     ("Hanabi env-only", "hn_4096", "env", "hn", 2, ("env wave", "observation waves"),
      {0: "move (transition, reward/done)", 1: "re-deals (wave shuffles)", 2: "publish snapshot",
       4: "field passes (bit vectors)", 5: "legal masks", 6: "write out + clear rows", 7: "barrier wait"}),
-    ("kitchen fused rollout", "oc_4096", "run", "oc", 0, ("env wave", "other waves"),
-     {0: "barrier at the step's top", 1: "layer 1", 2: "layer 2", 3: "layer 3", 4: "Gumbel scores",
-      5: "copy o_t to the trajectory (other waves)", 6: "barrier", 7: "argmax + barrier",
-      8: "transition (env lanes)", 9: "barrier",
-      10: "repaint o_t+1 (env lanes) / next step's noise (other waves; with no trajectory copy it is drawn during "
-          "the transition)"}),
+    ("kitchen fused rollout", "oc_4096", "run", "oc", 0,
+     ("env wave", "MLP waves 0-1", "MLP waves 2-7", "helper waves"),
+     {0: "barrier at the step's top", 1: "layer 1", 2: "barrier", 3: "layer 2", 4: "barrier",
+      5: "layer 3 + Gumbel argmax", 6: "barrier", 7: "transition (env lanes)",
+      8: "repaint o_t+1 (env lanes) / actions and logits out (helpers)", 9: "Gumbel noise",
+      10: "copy o_t to the trajectory"}),
     ("Hanabi fused rollout", "hn_4096", "run", "hn", 0, ("all waves",),
      {0: "barrier at the step's top", 1: "observation bit vectors", 2: "paint layer-1 tile", 3: "layer 1",
       4: "layer 2", 5: "layer 3", 6: "legal mask + Gumbel scores", 7: "copy o_t to the trajectory",

@@ -96,6 +96,36 @@ def test_packed_rollout_equals_unpacked(env, dims):
         assert torch.equal(packed[k], plain[k]), k
 
 
+@pytest.mark.parametrize("E", [1, 15, 17, 40])
+@pytest.mark.parametrize("keep", [("obs", "actions", "logits", "reward", "done", "obs_last"), ("reward",), ("obs_last",)])
+def test_kitchen_role_split_rollout(E, keep):
+    """256-wide packed kitchen policies run on a kernel of their own: ragged tiles of 16 kitchens, episodes that
+    end inside the launch, a launch split in two and outputs left out give the unpacked (general) kernel's
+    results, bit for bit."""
+    require_gpu()
+    _note(f"kitchen role-split rollout E={E} keep={keep}")
+    ws, bs = workloads.policy_weights((1170, 256, 256, 6), seed=31, bias_scale=0.3)
+    cfg = R.overcooked_config(E, cook_time=2, max_steps=9, env_base=77, seed=5)
+    res = []
+    for pack in (True, False):
+        pol = R.Policy(ws, bs, "bf16", pack=pack)
+        state = R.new_state(cfg)
+        R.rollout_init(cfg, state)
+        got = []
+        for t0, T in ((0, 13), (13, 1), (14, 10)):
+            out = dict(obs=torch.empty(T, E, 2, 1170, dtype=torch.bfloat16, device="cuda"),
+                       actions=torch.empty(T, E, 2, dtype=torch.int32, device="cuda"),
+                       logits=torch.empty(T, E, 2, 6, device="cuda"), reward=torch.empty(T, E, device="cuda"),
+                       done=torch.empty(T, E, dtype=torch.uint8, device="cuda"),
+                       obs_last=torch.empty(E, 2, 1170, dtype=torch.bfloat16, device="cuda"))
+            out = {k: v for k, v in out.items() if k in keep}
+            R.rollout_run(cfg, pol, state, t0, T, **out)
+            got += [out[k].cpu() for k in keep] + [state.cpu().clone()]
+        res.append(got)
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dims", [(432, 256, 256, 6), (658, 512, 512, 20), (1170, 256, 256, 6), (300, 512, 32, 20)])
 def test_packed_policy_forward_equals_unpacked(dims):
     """The tiled policy forward stages its weight slices from the packed copy: same logits, bit for bit."""
