@@ -21,6 +21,10 @@
 //   env    one LBF step with the sampled actions (the env-only kernels).
 // The heads dominate (2 x (H F + 2 F F) MACs per row): they are the GEMMs
 // that the MFMA roofline is taken on.
+//
+// Large batches of 1024-wide heads (s5_heads_fused) take three launches per
+// step instead: the front with fragment-major S5 matrices, each head with its
+// output layer in one kernel, and the env step.  4096 envs x 128 steps: 20.0 -> 13.3 ms.
 #include <mutex>
 #include "rl_internal.h"
 #include "rl_mlp.h"
@@ -539,6 +543,409 @@ __global__ __launch_bounds__(S5_NT) void s5_out_kernel(S5OutArgs o) {
   }
 }
 
+// ------------------------------------------- front, fragment-major weights ----
+//
+// s5_front_kernel for the batches whose heads run fused: the float32 S5 matrices
+// come from fragment-major copies (16 rows x 16 k per 1 KB: lane l holds
+// W[16 t + l % 16][16 j + 4 i + l / 16], i = 0..3, the operands of four MFMA K
+// steps), so each wave reads its own tiles straight into registers, FR_P blocks
+// ahead, with no staging through LDS and no barrier inside a product.  The products are taken
+// transposed (weights as the MFMA A operand): a lane ends with four consecutive
+// states or outputs of one row and moves the carried state 16 bytes at a time.
+// Same sums in the same order as s5_front_kernel: same bits.
+//
+// What bounds it: float32 MFMA (16,400 cycles per 32 rows at H = P = 128, one
+// workgroup per CU at 8192 rows), then the latency of the tile's loads.  8192 rows:
+// 30.1 us staged (which also multiplied every C x tile twice when H <= 128), 19.0 us here.
+constexpr int FR_P = 3;  // weight blocks in flight
+
+// Fragment-major copy of a float32 W [N x K], N and K multiples of 16.
+__global__ void s5_packf_kernel(int N, int K, const float* __restrict__ W, float* __restrict__ out) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;  // 16-byte lane block
+  if (v >= N * K / 4) return;
+  const int l = v & 63, tj = v >> 6, J = K / 16, j = tj % J, t = tj / J;
+  const float* w = W + (size_t)(16 * t + (l & 15)) * K + 16 * j + (l >> 4);
+  *reinterpret_cast<f32x4*>(out + (size_t)v * 4) = f32x4{w[0], w[4], w[8], w[12]};
+}
+
+// acc[g][m] = W tile tile[g] (16 outputs) times rows 16 m.. of the activations, K = 16 J;
+// act(m, k) is this lane's activation of row 16 m + lane % 16 at feature k + lane / 16.
+template <int G, int MT, typename Act>
+__device__ __forceinline__ void s5_frag_mma(const float* __restrict__ Wf, int J, const int (&tile)[G], int lane, Act act,
+                                            f32x4 (&acc)[G][MT]) {
+  auto load = [&](int g, int j) {
+    return *reinterpret_cast<const f32x4*>(Wf + ((size_t)(tile[g] * J + min(j, J - 1)) * 64 + lane) * 4);
+  };
+  f32x4 ring[FR_P][G];
+#pragma unroll
+  for (int q = 0; q < FR_P; ++q)
+#pragma unroll
+    for (int g = 0; g < G; ++g) ring[q][g] = load(g, q);
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[g][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 0; j0 < J; j0 += FR_P) {
+#pragma unroll
+    for (int q = 0; q < FR_P; ++q) {
+      if (j0 + q < J) {
+        float a[4][MT];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) a[i][m] = act(m, 16 * (j0 + q) + 4 * i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[g][m] = mfma_step(ring[q][g][i], a[i][m], acc[g][m]);
+#pragma unroll
+        for (int g = 0; g < G; ++g) ring[q][g] = load(g, j0 + q + FR_P);
+      }
+    }
+  }
+}
+
+struct S5FragLds {
+  int ldx, ldu, ldxf;
+  size_t off_u, off_xf, total;
+};
+__host__ __device__ inline S5FragLds s5_frag_lds(int D, int H, int P) {
+  S5FragLds L;
+  L.ldx = lds_ld<DT_BF16>(D);
+  L.ldu = lds_ld<DT_BF16>(H);
+  L.ldxf = 2 * P + 4;  // (4 mod 64 words when 2 P is a multiple of 64: operand reads on distinct banks)
+  L.off_u = ((size_t)S5_RT * L.ldx * 2 + 15) / 16 * 16;
+  L.off_xf = (L.off_u + (size_t)S5_RT * L.ldu * 2 + 15) / 16 * 16;
+  L.total = L.off_xf + (size_t)S5_RT * L.ldxf * 4;
+  return L;
+}
+
+// bf: fragment-major B_bar [2P, H]; cf: fragment-major [C_re | -C_im] [H, 2P].
+__global__ __launch_bounds__(S5F_NT) void s5_front_frag_kernel(S5FrontArgs a, const float* __restrict__ bf,
+                                                               const float* __restrict__ cf) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int MT = S5_RT / 16;
+  const S5FragLds L = s5_frag_lds(a.D, a.H, a.P);
+  uint16_t* xs = reinterpret_cast<uint16_t*>(smem);
+  uint16_t* us = reinterpret_cast<uint16_t*>(smem + L.off_u);
+  float* xf = reinterpret_cast<float*>(smem + L.off_xf);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = blockIdx.x * S5_RT;
+  const int D = a.D, H = a.H, P = a.P;
+  const int n4 = 4 * (lane >> 4);
+
+  // this wave's states: 16 wave .. + 15 (P <= 128); previous states of this lane's rows, zero where the
+  // row's episode starts at this observation (rows past the end read the last row)
+  const int p0 = (16 * wave < P ? 16 * wave : 0) + n4;
+  f32x4 xo[MT][2];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int row = min(r0 + 16 * m + (lane & 15), a.R - 1);
+    const bool keep = a.state[(size_t)a.step_plane * a.E + row / a.A] != 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(a.carry + (size_t)row * 2 * P + c * P + p0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xo[m][c][q] = keep ? v[q] : 0.f;
+    }
+  }
+  const f32x4 lr = *reinterpret_cast<const f32x4*>(a.lbar + p0), li = *reinterpret_cast<const f32x4*>(a.lbar + P + p0);
+  // observation tile (zero past D and past the last row)
+  if (D % 8 == 0) {
+    const int cpr = L.ldx / 8;
+    constexpr int CI = 2;
+    for (int i0 = tid; i0 < S5_RT * cpr; i0 += CI * S5F_NT) {
+      u32x4 v[CI];
+#pragma unroll
+      for (int j = 0; j < CI; ++j) {
+        const int i = i0 + j * S5F_NT, r = i / cpr, c = (i - r * cpr) * 8;
+        v[j] = (i < S5_RT * cpr && r0 + r < a.R && c < D)
+                   ? *reinterpret_cast<const u32x4*>(a.obs + (size_t)(r0 + r) * D + c)
+                   : u32x4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int j = 0; j < CI; ++j) {
+        const int i = i0 + j * S5F_NT, r = i / cpr, c = (i - r * cpr) * 8;
+        if (i < S5_RT * cpr) *reinterpret_cast<u32x4*>(xs + r * L.ldx + c) = v[j];
+      }
+    }
+  } else {
+    for (int i = tid; i < S5_RT * L.ldx; i += S5F_NT) {
+      const int r = i / L.ldx, c = i - r * L.ldx;
+      xs[i] = (r0 + r < a.R && c < D) ? a.obs[(size_t)(r0 + r) * D + c] : (uint16_t)0;
+    }
+  }
+  __syncthreads();
+  // u = tanh(W_enc o + b_enc), rounded to bf16
+  mlp_input_layer<DT_BF16>(xs, L.ldx, nullptr, S5_RT, D, a.w_enc, a.b_enc, H, us, L.ldu, wave, S5F_NW, lane);
+  __syncthreads();
+
+  // x_new = Lambda_bar x + B_bar u
+  if (16 * wave < P) {
+    const int tile[2] = {wave, P / 16 + wave};
+    f32x4 bu[2][MT];
+    s5_frag_mma<2, MT>(bf, H / 16, tile, lane,
+                       [&](int m, int k) { return bf16_to_f32(us[(16 * m + (lane & 15)) * L.ldu + k + (lane >> 4)]); }, bu);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int rl = 16 * m + (lane & 15), row = r0 + rl;
+      f32x4 nr, ni;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float xr = xo[m][0][q], xi = xo[m][1][q];
+        nr[q] = lr[q] * xr - li[q] * xi + bu[0][m][q];
+        ni[q] = lr[q] * xi + li[q] * xr + bu[1][m][q];
+      }
+      *reinterpret_cast<f32x4*>(xf + rl * L.ldxf + p0) = nr;
+      *reinterpret_cast<f32x4*>(xf + rl * L.ldxf + P + p0) = ni;
+      if (a.commit && row < a.R) {
+        *reinterpret_cast<f32x4*>(a.carry + (size_t)row * 2 * P + p0) = nr;
+        *reinterpret_cast<f32x4*>(a.carry + (size_t)row * 2 * P + P + p0) = ni;
+      }
+    }
+  }
+  __syncthreads();
+
+  // y = [C_re | -C_im] [x_re | x_im] + D u, rounded to bf16: wave w takes output tiles w and w + 8
+  for (int ht = wave; ht < H / 16; ht += S5F_NW) {
+    const int tile[1] = {ht};
+    f32x4 cy[1][MT];
+    s5_frag_mma<1, MT>(cf, 2 * P / 16, tile, lane,
+                       [&](int m, int k) { return xf[(16 * m + (lane & 15)) * L.ldxf + k + (lane >> 4)]; }, cy);
+    const int h0 = 16 * ht + n4;
+    const f32x4 dh = *reinterpret_cast<const f32x4*>(a.d + h0);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int rl = 16 * m + (lane & 15), row = r0 + rl;
+      const uint2 uw = *reinterpret_cast<const uint2*>(us + rl * L.ldu + h0);
+      const float u0 = bf16_to_f32((uint16_t)(uw.x & 0xffffu)), u1 = bf16_to_f32((uint16_t)(uw.x >> 16));
+      const float u2 = bf16_to_f32((uint16_t)(uw.y & 0xffffu)), u3 = bf16_to_f32((uint16_t)(uw.y >> 16));
+      uint2 v;
+      v.x = pack_bf16x2(cy[0][m][0] + dh[0] * u0, cy[0][m][1] + dh[1] * u1);
+      v.y = pack_bf16x2(cy[0][m][2] + dh[2] * u2, cy[0][m][3] + dh[3] * u3);
+      if (row < a.R) *reinterpret_cast<uint2*>(a.y + (size_t)row * H + h0) = v;
+    }
+  }
+}
+
+// --------------------------------------------------------- fused heads ----
+//
+// All of one head on 64 rows in one workgroup: the three tanh layers with the
+// activations in LDS (one buffer, overwritten after a layer's last read) and
+// the output layer with sampling (actor) or the value (critic).  8 waves; wave
+// w owns units w F / 8 .. of every row, so each weight byte goes once from L2
+// straight into one wave's MFMA operand registers, from a fragment-major copy
+// (1 KB contiguous per load) that the rollout writes into the workspace, two K
+// steps ahead (the next layer's first ones before a layer's epilogue).
+// Blocks go to the XCDs round-robin: XCDs 0-3 run actor tiles, 4-7 critic tiles, so an
+// L2 carries one head's weights.
+//
+// The products, the K order and the output layer's four K-quarter sums are
+// those of s5_head_gemm_kernel and s5_out_kernel: same bits.
+//
+// What bounds it: a K step is 1024 MFMA cycles per SIMD (two waves) against 64 KB
+// of weights into the CU, which takes 1100-1300 cycles; 8192 rows of H 128 measured
+// 78 us (three GEMM launches and the output kernel: 120 us), 60 us of them without
+// the weight loads (the clock falls to about 1.9 GHz) and about 8 us less without the
+// tanh epilogues, which nothing overlaps.
+constexpr int HF_BM = 64, HF_NT = 512;
+
+struct HeadFusedArgs {
+  const uint16_t* y;         // [R, H]
+  const uint16_t* packed;    // two heads of hf_packed_elems(H, F), layers 0..2 in turn
+  const uint16_t* b[2][3];
+  int H;
+  S5OutArgs o;               // output layer (ha / hc unused)
+};
+
+__host__ __device__ inline size_t hf_packed_elems(int H, int F) { return (size_t)F * H + 2 * (size_t)F * F; }
+
+// Bytes of the copies a fused rollout makes: the heads' matrices, B_bar and [C_re | -C_im].
+__host__ __device__ inline size_t s5_fused_bytes(int H, int F, int P) {
+  return 2 * hf_packed_elems(H, F) * 2 + 2 * (size_t)H * 2 * P * 4;
+}
+
+// Fragment-major copies of the six hidden-layer matrices: blockIdx.y = head * 3 + layer.
+struct HeadPackArgs {
+  const uint16_t* w[6];
+  int H, F;
+  uint16_t* out;
+};
+
+__global__ void s5_pack_kernel(HeadPackArgs a) {
+  const int z = blockIdx.y / 3, l = blockIdx.y % 3, K = l == 0 ? a.H : a.F, S = K / 32;
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;  // 16-byte operand block
+  if (v >= a.F * K / 8) return;
+  const int lane = v & 63, ts = v >> 6, s = ts % S, t = ts / S;
+  const size_t base = (size_t)z * hf_packed_elems(a.H, a.F) + (l == 0 ? 0 : (size_t)a.F * a.H + (size_t)(l - 1) * a.F * a.F);
+  *reinterpret_cast<u32x4*>(a.out + base + (size_t)v * 8) =
+      *reinterpret_cast<const u32x4*>(a.w[blockIdx.y] + (size_t)(16 * t + (lane & 15)) * K + 32 * s + 8 * (lane >> 4));
+}
+
+__global__ __launch_bounds__(HF_NT) void s5_heads_kernel(HeadFusedArgs g) {
+  constexpr int F = 1024, UT = F / 128 /* unit tiles per wave */, LDH = F + 8, MT = HF_BM / 16;
+  extern __shared__ __align__(16) uint8_t smem[];
+  uint16_t* hs = reinterpret_cast<uint16_t*>(smem);
+  float* lp = reinterpret_cast<float*>(smem + (size_t)HF_BM * LDH * 2);  // [4][HF_BM][17] K-quarter sums
+  float* lgs = lp + 4 * HF_BM * 17;                                      // [HF_BM][17] logits, then scores
+  float* scs = lgs + HF_BM * 17;
+  const S5OutArgs& o = g.o;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int z = (blockIdx.x & 7) >> 2;
+  const int r0 = ((blockIdx.x >> 3) * 4 + (blockIdx.x & 3)) * HF_BM;
+  if (r0 >= o.R || (z == 0 && !o.sample)) return;
+  const int H = g.H, nrow = min(HF_BM, o.R - r0);
+
+  // y tile (rows past the end repeat the last row; their results are not stored)
+  for (int i = tid; i < HF_BM * (H / 8); i += HF_NT) {
+    const int r = i / (H / 8), c = (i - r * (H / 8)) * 8;
+    *reinterpret_cast<u32x4*>(hs + r * LDH + c) =
+        *reinterpret_cast<const u32x4*>(g.y + (size_t)min(r0 + r, o.R - 1) * H + c);
+  }
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(g.packed + z * hf_packed_elems(H, F)), (short)0, (int)(hf_packed_elems(H, F) * 2), 0x00020000);
+  // operand of unit tile UT wave + u, K step st of the layer at byte offset `base` with S K steps
+  auto w_load = [&](int base, int S, int u, int st) -> u32x4 {
+    return __builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16, base + ((UT * wave + u) * S + st) * 1024, 0);
+  };
+  u32x4 wr[2][UT];
+  const int S0 = H / 32, SF = F / 32;
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int u = 0; u < UT; ++u) wr[kk][u] = w_load(0, S0, u, kk);
+  __syncthreads();
+
+  const uint16_t* hb = hs + (lane & 15) * LDH + 8 * (lane >> 4);
+  for (int l = 0; l < 3; ++l) {
+    const int S = l == 0 ? S0 : SF;
+    const int base = l == 0 ? 0 : (F * H + (l - 1) * F * F) * 2, nbase = (F * H + l * F * F) * 2;
+    f32x4 acc[UT][MT];
+#pragma unroll
+    for (int u = 0; u < UT; ++u)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) acc[u][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 b[2][MT];  // row operands of K steps st and st + 1 (slot = st % 2), each read one step ahead
+#pragma unroll
+    for (int m = 0; m < MT; ++m) b[0][m] = *reinterpret_cast<const u32x4*>(hb + m * 16 * LDH);
+    for (int st = 0; st < S; st += 2) {
+      const bool more = st + 2 < S;  // else: the next layer's K steps 0 and 1 (past the last layer: unused)
+      const int fb = more ? base + (st + 2) * 1024 : nbase, fs = more ? S : SF;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+          b[1 - kk][m] = *reinterpret_cast<const u32x4*>(hb + m * 16 * LDH + min(st + kk + 1, S - 1) * 32);
+        __builtin_amdgcn_sched_barrier(0);  // (keeps those reads ahead of this step's MFMAs)
+#pragma unroll
+        for (int u = 0; u < UT; ++u) {
+#pragma unroll
+          for (int m = 0; m < MT; ++m) acc[u][m] = mfma_step(wr[kk][u], b[kk][m], acc[u][m]);
+          wr[kk][u] = w_load(fb, fs, u, kk);
+        }
+      }
+    }
+    __syncthreads();  // every wave is past its last read of the layer's input
+    const uint16_t* __restrict__ bias = g.b[z][l];
+#pragma unroll
+    for (int u = 0; u < UT; ++u) {
+      const int u0 = (UT * wave + u) * 16 + 4 * (lane >> 4);
+      const uint2 bw = *reinterpret_cast<const uint2*>(bias + u0);
+      const float b0 = bf16_to_f32((uint16_t)(bw.x & 0xffffu)), b1 = bf16_to_f32((uint16_t)(bw.x >> 16));
+      const float b2 = bf16_to_f32((uint16_t)(bw.y & 0xffffu)), b3 = bf16_to_f32((uint16_t)(bw.y >> 16));
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        uint2 v;
+        v.x = pack_bf16x2(fast_tanh(acc[u][m][0] + b0), fast_tanh(acc[u][m][1] + b1));
+        v.y = pack_bf16x2(fast_tanh(acc[u][m][2] + b2), fast_tanh(acc[u][m][3] + b3));
+        *reinterpret_cast<uint2*>(hs + (16 * m + (lane & 15)) * LDH + u0) = v;
+      }
+    }
+    __syncthreads();
+  }
+
+  // output layer: item (row tile, K quarter) per wave, two each
+  const int n = lane & 15, nout = z == 0 ? o.NA : 1;
+  const uint16_t* w3 = (z == 0 ? o.wa : o.wc) + (size_t)(n < nout ? n : 0) * F + 8 * (lane >> 4);
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  constexpr int KQ = F / 4;
+  for (int item = wave; item < MT * 4; item += HF_NT / 64) {
+    const int m = item & (MT - 1), q = item / MT;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KQ; k += 32) {
+      const u32x4 w = *reinterpret_cast<const u32x4*>(w3 + q * KQ + k);
+      acc = mfma_step(*reinterpret_cast<const u32x4*>(hb + m * 16 * LDH + q * KQ + k), n < nout ? w : zero, acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lp[(q * HF_BM + 16 * m + 4 * (lane >> 4) + r) * 17 + n] = acc[r];
+  }
+  __syncthreads();
+  auto sum_quarters = [&](float x, int r, int k) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x += lp[(q * HF_BM + r) * 17 + k];
+    return x;
+  };
+  if (z == 1) {
+    if (tid < nrow && o.value) o.value[r0 + tid] = sum_quarters(bf16_to_f32(o.bc[0]), tid, 0);
+    return;
+  }
+  for (int i = tid; i < HF_BM * 16; i += HF_NT) {
+    const int r = i >> 4, k = i & 15, row = r0 + r;
+    if (k < o.NA && r < nrow) {
+      const float x = sum_quarters(bf16_to_f32(o.ba[k]), r, k);
+      const int e = row / o.A, ag = row - e * o.A;
+      lgs[r * 17 + k] = x;
+      scs[r * 17 + k] = action_score(x, action_noise(o.seed, (uint64_t)(o.env_base + e), o.t, ag, k), true);
+      if (o.logits) o.logits[(size_t)row * o.NA + k] = x;
+    }
+  }
+  __syncthreads();
+  if (tid < nrow) {
+    const int row = r0 + tid;
+    int best = 0;
+    float bs = -INFINITY;
+    for (int k = 0; k < o.NA; ++k)
+      if (scs[tid * 17 + k] > bs) {
+        bs = scs[tid * 17 + k];
+        best = k;
+      }
+    o.actions[row] = best;
+    if (o.logp) o.logp[row] = log_softmax_at(lgs + tid * 17, o.NA, best);
+  }
+}
+
+constexpr int HF_F = 1024;
+constexpr size_t HF_LDS = (size_t)HF_BM * (HF_F + 8) * 2 + (4 + 2) * HF_BM * 17 * 4;
+static_assert(HF_LDS <= MAX_LDS_BYTES, "one workgroup per CU");
+
+// The fused heads serve F = 1024 (activations of 64 rows in LDS, 8 unit tiles per
+// wave) from the batch size on at which they are faster.  A round of 256 workgroups
+// (8192 rows) takes about 78 us full or not; the three GEMMs and the output kernel
+// 14 us and 13 us per 1000 rows: 4096 rows measured the same, 6000 rows 79
+// against 104 us per step, 8192 rows 78 against 120, 16384 rows 160 against 225.
+// (At these sizes the weights' copy also fits where the GEMM path keeps its
+// activations.)
+static bool s5_heads_fused(int R, int H, int F) {
+  const int64_t rounds = (2 * (((int64_t)R + HF_BM - 1) / HF_BM) + 255) / 256;
+  return F == HF_F && R >= 6144 * rounds - 2048 && s5_fused_bytes(H, F, 128) <= (size_t)4 * R * F * 2;
+}
+
+static hipError_t launch_s5_heads(const HeadFusedArgs& g, hipStream_t s) {
+  static bool attr = false;
+  if (!attr) {
+    const hipError_t e = hipFuncSetAttribute((const void*)s5_heads_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)HF_LDS);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  const int tiles = (g.o.R + HF_BM - 1) / HF_BM;
+  s5_heads_kernel<<<dim3((unsigned)((tiles + 3) / 4 * 8)), HF_NT, HF_LDS, s>>>(g);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------- the loop ----
 
 static size_t align256(size_t x) { return (x + 255) / 256 * 256; }
@@ -612,6 +1019,9 @@ hipError_t launch_s5_rollout(const LbfParams& p, const S5Net& net, int32_t* stat
   if (!attr) {
     hipError_t e = hipFuncSetAttribute((const void*)s5_front_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)MAX_LDS_BYTES);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)s5_front_frag_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)MAX_LDS_BYTES);
     if (e != hipSuccess) return e;
     attr = true;
   }
@@ -637,10 +1047,20 @@ hipError_t launch_s5_rollout(const LbfParams& p, const S5Net& net, int32_t* stat
   const dim3 head_grid((unsigned)(2 * mtiles * (F / HG_BN)));
   const dim3 out_grid((unsigned)((R + 15) / 16));
 
+  const bool fused = s5_heads_fused(R, H, F);
+  HeadFusedArgs hf{};
+  float* bfrag = reinterpret_cast<float*>(hbuf + 2 * hf_packed_elems(H, F));  // (16-byte aligned: whole KB blocks)
+  float* cfrag = bfrag + (size_t)2 * net.P * H;
+  const size_t frag_lds = s5_frag_lds(D, H, net.P).total;
   // the policy on the observations in obs_slot(k): y, the three head layers, then the output kernel
   auto policy = [&](int k, int commit, const S5OutArgs& oa) -> hipError_t {
     fa.obs = obs_slot(k);
     fa.commit = commit;
+    if (fused) {
+      s5_front_frag_kernel<<<front_grid, S5F_NT, frag_lds, s>>>(fa, bfrag, cfrag);
+      hf.o = oa;
+      return launch_s5_heads(hf, s);
+    }
     s5_front_kernel<<<front_grid, S5F_NT, front_lds, s>>>(fa);
     HeadGemmArgs g{};
     g.M = R;
@@ -679,6 +1099,25 @@ hipError_t launch_s5_rollout(const LbfParams& p, const S5Net& net, int32_t* stat
 
   s5_cat_kernel<<<dim3((unsigned)((H * 2 * net.P + 255) / 256)), 256, 0, s>>>(
       H, net.P, net.c, reinterpret_cast<float*>(ws + W.off_wcat));
+  if (fused) {
+    HeadPackArgs pk{};
+    for (int l = 0; l < 3; ++l) {
+      pk.w[l] = static_cast<const uint16_t*>(net.actor_w[l]);
+      pk.w[3 + l] = static_cast<const uint16_t*>(net.critic_w[l]);
+      hf.b[0][l] = static_cast<const uint16_t*>(net.actor_b[l]);
+      hf.b[1][l] = static_cast<const uint16_t*>(net.critic_b[l]);
+    }
+    pk.H = H;
+    pk.F = F;
+    pk.out = hbuf;
+    hf.y = ybuf;
+    hf.packed = hbuf;
+    hf.H = H;
+    s5_pack_kernel<<<dim3((unsigned)((F * F / 8 + 255) / 256), 6), 256, 0, s>>>(pk);
+    const dim3 pf((unsigned)((H * 2 * net.P / 4 + 255) / 256));
+    s5_packf_kernel<<<pf, 256, 0, s>>>(2 * net.P, H, net.bbar, bfrag);
+    s5_packf_kernel<<<pf, 256, 0, s>>>(H, 2 * net.P, reinterpret_cast<const float*>(ws + W.off_wcat), cfrag);
+  }
   hipError_t err = launch_lbf_observe(p, state, obs_slot(0), s);
   if (err != hipSuccess) return err;
   for (int k = 0; k < n_steps; ++k) {

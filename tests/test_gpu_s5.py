@@ -173,3 +173,30 @@ def test_s5_rollout_4096_sampled_envs():
     assert set(np.unique(done)) <= {0, 1, 2, 3}
     assert ((done != 0).sum(axis=0) >= 2).all()
     assert torch.isfinite(g["logits"]).all() and torch.isfinite(g["value"]).all()
+
+
+@pytest.mark.parametrize("H,P,E", [(64, 16, 2049), (128, 128, 2079), (256, 48, 2064)])
+def test_fused_heads_equal_gemm_heads(H, P, E):
+    """From 4096 rows on each head runs in one workgroup per 64 rows and the front reads fragment-major S5
+    matrices; smaller batches run three GEMMs.  The envs that a large (ragged) and a small batch share have the
+    same trajectories, values, log-probabilities and carried states, bit for bit."""
+    require_gpu()
+    _note(f"S5 fused heads H={H} P={P} E={E}")
+    small, T = 77, 5
+    pol = R.S5Policy(workloads.s5_params(192, H, P, 1024, 6, seed=9))
+    res = []
+    for n in (E, small):
+        cfg = R.EnvConfig(n_envs=n, seed=3, max_steps=3, env_base=0 if n == E else E - small)
+        state = R.new_state(cfg)
+        R.rollout_init(cfg, state)
+        carry = torch.zeros(n * 2, 2, P, device="cuda")
+        out = dict(obs=torch.empty(T, n, 2, 192, dtype=torch.bfloat16, device="cuda"),
+                   actions=torch.empty(T, n, 2, dtype=torch.int32, device="cuda"),
+                   logits=torch.empty(T, n, 2, 6, device="cuda"), reward=torch.empty(T, n, device="cuda"),
+                   value=torch.empty(T, n, 2, device="cuda"), logp=torch.empty(T, n, 2, device="cuda"))
+        last = torch.empty(n, 2, device="cuda")
+        R.rollout_run_s5(cfg, pol, state, carry, 0, T, value_last=last, **out)
+        torch.cuda.synchronize()
+        res.append([v[:, -small:].cpu() for v in out.values()] + [last[-small:].cpu(), carry[-2 * small:].cpu()])
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
