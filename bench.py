@@ -538,7 +538,12 @@ PHASE_CASES = (
      {0: "barrier at the step's top", 1: "action Philox draws (one step in 16)", 2: "layer 1 + barrier",
       3: "layer 2 + barrier", 4: "layer 3 + Gumbel argmax", 5: "transition", 6: "resets",
       7: "paint o_t+1, reward/done stores", 8: "copy o_t to the trajectory", 9: "Gumbel noise of step t+1"}),
-    ("12x12 fused rollout", "lbf12_16k", "run", "lbf", 0, ("env wave", "other waves"), None),
+    ("12x12 fused rollout", "lbf12_16k", "run", "lbf", 0,
+     ("env wave", "MLP waves 0-2", "MLP waves 3-7", "helper waves"),
+     {0: "barrier at the step's top", 1: "layer 1", 2: "barrier", 3: "layer 2", 4: "barrier",
+      5: "layer 3 + Gumbel argmax", 6: "barrier", 7: "moves and loads (env quads)",
+      8: "resets, repaint o_t+1 (env quads) / actions, logits, next draws (helpers)", 9: "Gumbel noise",
+      10: "copy o_t to the trajectory"}),
     ("Hanabi env-only", "hn_4096", "env", "hn", 2, ("env wave", "observation waves"),
      {0: "move (transition, reward/done)", 1: "re-deals (wave shuffles)", 2: "publish snapshot",
       4: "field passes (bit vectors)", 5: "legal masks", 6: "write out + clear rows", 7: "barrier wait"}),
@@ -619,7 +624,6 @@ def phases():
           "The stamps add waits of their own (each mark waits for the wave's outstanding LDS operations), so "
           "the launch takes longer than in the product build: read the split, not the total.", ""]
     for (case, name, call, unit, extra, roles, names), rr in zip(PHASE_CASES, res):
-        names = names or PHASE_CASES[0][6]
         tab = rr["table"]
         md += [f"## {case} ({name}, {call}; stamped launch {rr['ms']:.3f} ms, {rr['iterations']} iterations)", "",
                "| phase | " + " | ".join(roles) + " |", "|---|" + "---|" * len(roles)]

@@ -814,9 +814,8 @@ __device__ __forceinline__ float row_log_pi(const float (&logit)[4], int g, int 
 
 // Same step as lbf_run_kernel for compile-time policy sizes, restructured for
 // latency:
-//   * layer-1/2 weights live in registers (S1: layer 1 streamed from the
-//     packed copy) and layer 3 in LDS for the whole rollout; layers are
-//     computed transposed so each lane ends with four consecutive outputs of
+//   * layer-1/2 weights live in registers and layer 3 in LDS for the whole
+//     rollout; layers are computed transposed so each lane ends with four consecutive outputs of
 //     one row, with all of a layer's LDS operands read ahead of its MFMAs;
 //   * observations are painted by the env lanes straight into the layer-1
 //     operand tile (only the non-zero features are written); with two tiles
@@ -839,7 +838,7 @@ __device__ __forceinline__ float row_log_pi(const float (&logit)[4], int g, int 
 // TM: agents whose teammates entry is a heuristic kind act with that
 // heuristic (evaluated by the env lanes) instead of the network.
 template <int DT, int GH, int GW, int H1, int H2, int NA, int A, int F, int TE, int NW, int MINB, bool VH = false,
-          bool TM = false, bool S1 = false>
+          bool TM = false>
 __global__ __launch_bounds__(NW * 64, MINB) void lbf_rollout_kernel(LbfParams p, PolicyArgs pol,
                                                                     int32_t* __restrict__ state, uint64_t t0,
                                                                     int n_steps, TrajArgs out) {
@@ -861,11 +860,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void lbf_rollout_kernel(LbfParams p,
   // LEAN: the resident weights leave too few registers for the env step, so
   // the biases and the env state wait in LDS between uses.
   constexpr int REG_BUDGET = 512 / ((NW * MINB + 3) / 4);
-  // S1: layer 1 streams its weights from L2 (StreamLayer) instead of holding them
-  constexpr int L1REGS = S1 ? StreamLayer<DT_BF16, D, H1, NW>::WREGS : RegLayer<DT, D, H1, NW>::WREGS;
-  constexpr bool LEAN = S1 || L1REGS + RegLayer<DT, H1, H2, NW>::WREGS + 160 > REG_BUDGET;
-  using L1T = std::conditional_t<S1, StreamLayer<DT_BF16, D, H1, NW, LEAN>, RegLayer<DT, D, H1, NW, LEAN>>;
-  static_assert(!S1 || DT == DT_BF16, "streamed layer 1: bf16");
+  constexpr bool LEAN = RegLayer<DT, D, H1, NW>::WREGS + RegLayer<DT, H1, H2, NW>::WREGS + 160 > REG_BUDGET;
+  using L1T = RegLayer<DT, D, H1, NW, LEAN>;
   constexpr int NOUT = NA + (VH ? 1 : 0);  // layer-3 outputs: the actions, then the value
   static_assert(NA <= 8 && NOUT <= 8, "one Philox block of action noise per row; outputs in two lane groups");
   static_assert(!(VH && LEAN), "the value head runs on shapes whose env state stays in registers");
@@ -912,10 +908,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void lbf_rollout_kernel(LbfParams p,
     for (int i = tid; i < H1 + H2; i += NT)
       bias_s[i] = DType<DT>::to_f32(i < H1 ? static_cast<const T*>(pol.b[0])[i] : static_cast<const T*>(pol.b[1])[i - H1]);
   }
-  if constexpr (S1)
-    L1.load(static_cast<const T*>(pol.b[0]), wave, lane, static_cast<const T*>(pol.Wp[0]));
-  else
-    L1.load(static_cast<const T*>(pol.W[0]), static_cast<const T*>(pol.b[0]), wave, lane);
+  L1.load(static_cast<const T*>(pol.W[0]), static_cast<const T*>(pol.b[0]), wave, lane);
   L2.load(static_cast<const T*>(pol.W[1]), static_cast<const T*>(pol.b[1]), wave, lane);
   if (tid < 64) {
     const int n = lane & 15;
@@ -1000,12 +993,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void lbf_rollout_kernel(LbfParams p,
       L2.template run<MT>(h1s, LD1, acc, wave, lane);
       // (one tile) o_t to the trajectory while the layer-2 MFMAs run, clearing
       // the tile behind the copy (the env wave paints o_{t+1} onto it after layer 3)
-      if constexpr (!DB) {
-        int ct = tid;
-        if constexpr (S1) asm volatile("" : "+v"(ct));  // (its addresses formed here, not held across the loop)
+      if constexpr (!DB)
         copy_obs_rows<T, R, D, LDX, NT, true>(
-            xcur, out.obs ? static_cast<T*>(out.obs) + ((size_t)k * E + e0) * A * D : nullptr, te_valid * A, ct);
-      }
+            xcur, out.obs ? static_cast<T*>(out.obs) + ((size_t)k * E + e0) * A * D : nullptr, te_valid * A, tid);
       L2.template store_tanh<MT>(acc, h2s, LD2, wave, lane, bias_s + H1);
     }
     __syncthreads();
@@ -1229,14 +1219,433 @@ __global__ __launch_bounds__(NW * 64, MINB) void lbf_rollout_kernel(LbfParams p,
   if (envlane) lbf_store<A, F>(state, p, e, s);
 }
 
+// ------------------- fused rollout, 256-wide packed bf16 policies ----
+//
+// The rollout of lbf_rollout_kernel for grids and policies whose weights do
+// not fit the register file (12x12, 3 agents, 432-256-256-6), from the packed
+// copy.  16 envs per workgroup, one workgroup per CU, 12 waves by role:
+//   waves 0-7   the MLP: unit tiles 2 w and 2 w + 1 of layers 1 and 2 for the A row
+//               tiles.  Layer 2's weights stay in registers, layer 3's and the
+//               last FS_LK K steps of layer 1's in LDS; the rest of layer 1
+//               streams from L2, its first K steps fetched while the envs step.
+//               Waves 0 .. A - 1 also run layer 3 and the Gumbel argmax of one row tile
+//               each.  These waves store nothing to global memory: a load waits
+//               for its wave's earlier stores.
+//   wave 8      the env wave: a quad of lanes per env, each holding the env's
+//               state.  Lane q moves agent q, resolves foods q and q + 4 and repaints
+//               the observation row of agent q (erasing what moved); targets and
+//               eaten foods cross the quad by DPP.
+//   waves 8-11  under layers 1 and 2: the step's Gumbel noise from its Philox
+//               draws, and the copy of o_t to the trajectory;
+//   waves 9-11  while the envs step: the actions and logits out, the next step's draws.
+// Every layer's sums run over K in the order of lbf_rollout_kernel: same bits.
+//
+// What bounds it: of about 14,000 stamped cycles per step layer 1 takes 6,400
+// (2,700 of MFMA per SIMD, 1,600 of tanh, 176 KB of streamed weights and 41 KB of
+// trajectory through the CU's path to L2), layer 2 3,800, layer 3 and the argmax
+// 1,000, the env quads 2,500.  16384 envs x 128 steps: 4.08 ms in the kernel that
+// ran every part on all waves in turn, 2.93 ms here; three K steps in flight
+// spill (2.98).
+template <int GH, int GW, int A, int F>
+struct LbfFs {
+  static constexpr int NT = 768, TE = 16, R = TE * A, MT = A, HW = GH * GW, D = 3 * HW;
+  static constexpr int H = 256, LDH = H + 8, LDX = lds_ld<DT_BF16>(D);
+  static constexpr int S1 = (D + 31) / 32, S2 = H / 32;
+  static constexpr int LK = 3, P = 2;  // layer-1 K steps held in LDS; in flight
+  static constexpr int CB = 32;        // rows of o_t copied under layer 1
+  struct Lds {
+    uint16_t xs[R * LDX];              // o_t
+    uint16_t h1[R * LDH], h2[R * LDH];
+    u32x4 w1[LK * (H / 16) * 64];      // layer-1 operands of the last K steps: (step, tile, lane)
+    u32x4 w3[S2 * 64];                 // layer-3 operands: (step, lane)
+    float bias[2 * H];
+    float nz[R * 8], lg[R * 8];        // the step's Gumbel noise and logits, by (row, action)
+    uint32_t words[R * 8];             // the step's action draws
+    uint32_t rdraw[TE * LBF_MAX_DRAWS];
+    int act[R];
+    float b3[8];
+  };
+  static_assert(sizeof(Lds) <= MAX_LDS_BYTES, "one workgroup per CU");
+  static_assert(A <= 4 && F <= 8 && TE * ((2 * A + 2 * F + 7) / 8) <= 64, "a quad per env; one lane per reset block");
+  static_assert(R <= 64 && D % 8 == 0, "a lane per row's draws; whole-vector rows");
+};
+
+template <int GH, int GW, int A, int F>
+__global__ __launch_bounds__(768) void lbf_run_fs_kernel(LbfParams p, PolicyArgs pol, int32_t* __restrict__ state,
+                                                         uint64_t t0, int n_steps, TrajArgs out) {
+  using C = LbfFs<GH, GW, A, F>;
+  constexpr int NA = LBF_NACT, NS = C::S1 - C::LK, MT = C::MT, HW = C::HW, R = C::R, TE = C::TE;
+  extern __shared__ __align__(16) uint8_t smem[];
+  typename C::Lds& L = *reinterpret_cast<typename C::Lds*>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int e0 = blockIdx.x * TE, te_valid = min(TE, p.E - e0), E = p.E;
+  const uint16_t* Wp1 = static_cast<const uint16_t*>(pol.Wp[0]);
+  const uint16_t* Wp2 = static_cast<const uint16_t*>(pol.Wp[1]);
+  const uint16_t* Wp3 = static_cast<const uint16_t*>(pol.Wp[2]);
+  auto block = [](const uint16_t* Wp, int S, int tile, int ks, int ln) {
+    return *reinterpret_cast<const u32x4*>(Wp + ((size_t)(tile * S + ks) * 64 + ln) * 8);
+  };
+  zero_lds<C::NT>(smem, sizeof(typename C::Lds), tid);
+  __syncthreads();
+  for (int i = tid; i < C::LK * (C::H / 16) * 64; i += C::NT) {
+    const int q = i / (C::H / 16 * 64), r = i - q * (C::H / 16 * 64);
+    L.w1[i] = block(Wp1, C::S1, r >> 6, NS + q, r & 63);
+  }
+  for (int i = tid; i < C::S2 * 64; i += C::NT) L.w3[i] = block(Wp3, C::S2, 0, i >> 6, i & 63);
+  for (int i = tid; i < 2 * C::H; i += C::NT)
+    L.bias[i] = bf16_to_f32(i < C::H ? static_cast<const uint16_t*>(pol.b[0])[i]
+                                     : static_cast<const uint16_t*>(pol.b[1])[i - C::H]);
+  if (tid < NA) L.b3[tid] = bf16_to_f32(static_cast<const uint16_t*>(pol.b[2])[tid]);
+
+  if (wave < 8) {
+    // ------------------------------------------------------------- MLP ----
+    u32x4 w2[C::S2][2], ring[C::P][2];
+#pragma unroll
+    for (int ks = 0; ks < C::S2; ++ks)
+#pragma unroll
+      for (int o = 0; o < 2; ++o) w2[ks][o] = block(Wp2, C::S2, 2 * wave + o, ks, lane);
+    int ln = lane;
+    auto fetch = [&](int ks, u32x4 (&dst)[2]) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) dst[o] = block(Wp1, C::S1, 2 * wave + o, ks, ln);
+    };
+#pragma unroll
+    for (int q = 0; q < C::P; ++q) fetch(q, ring[q]);
+    // tanh(acc + bias) of row tile m, owned tile o: four consecutive units of one row per lane
+    auto store_tanh = [&](const f32x4 (&acc)[MT][2], const float* bias, uint16_t* dst) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        const int u0 = (2 * wave + o) * 16 + 4 * (lane >> 4);
+        const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + u0);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = fast_tanh(acc[m][o][r] + b4[r]);
+          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+          *reinterpret_cast<u32x2*>(dst + (16 * m + (lane & 15)) * C::LDH + u0) =
+              u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
+      }
+    };
+    const uint16_t* xrow = L.xs + (lane & 15) * C::LDX + 8 * (lane >> 4);
+    const uint16_t* h1row = L.h1 + (lane & 15) * C::LDH + 8 * (lane >> 4);
+    RL_STAMP_BEGIN
+    for (int k = 0; k < n_steps; ++k) {
+      // (an opaque lane index: the weight loads of every step are the same and
+      // would otherwise be hoisted out of the step loop)
+      asm volatile("" : "+v"(ln));
+      __syncthreads();  // o_t is painted, its action draws made
+      RL_STAMP(0)
+      {
+        f32x4 acc[MT][2];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int o = 0; o < 2; ++o) acc[m][o] = f32x4{0.f, 0.f, 0.f, 0.f};
+        u32x4 a[2][MT];  // row operands of K steps ks (slot ks % 2) and ks + 1
+#pragma unroll
+        for (int m = 0; m < MT; ++m) a[0][m] = *reinterpret_cast<const u32x4*>(xrow + m * 16 * C::LDX);
+#pragma unroll
+        for (int ks = 0; ks < C::S1; ++ks) {
+          if (ks + 1 < C::S1) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+              a[(ks + 1) & 1][m] = *reinterpret_cast<const u32x4*>(xrow + m * 16 * C::LDX + (ks + 1) * 32);
+          }
+          u32x4 w[2];
+#pragma unroll
+          for (int o = 0; o < 2; ++o)
+            w[o] = ks < NS ? ring[ks % C::P][o] : L.w1[((ks - NS) * (C::H / 16) + 2 * wave + o) * 64 + lane];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m][o] = mfma_step(w[o], a[ks & 1][m], acc[m][o]);
+          if (ks + C::P < NS) fetch(ks + C::P, ring[ks % C::P]);
+        }
+        // the first K steps of the next env step (the last fetch of a launch goes unused)
+#pragma unroll
+        for (int q = 0; q < C::P; ++q) fetch(q, ring[q]);
+        store_tanh(acc, L.bias, L.h1);
+      }
+      RL_STAMP(1)
+      __syncthreads();  // h1
+      RL_STAMP(2)
+      {
+        f32x4 acc[MT][2];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int o = 0; o < 2; ++o) acc[m][o] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < C::S2; ++ks) {
+          u32x4 a[MT];
+#pragma unroll
+          for (int m = 0; m < MT; ++m) a[m] = *reinterpret_cast<const u32x4*>(h1row + m * 16 * C::LDH + ks * 32);
+#pragma unroll
+          for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m][o] = mfma_step(w2[ks][o], a[m], acc[m][o]);
+        }
+        store_tanh(acc, L.bias + C::H, L.h2);
+      }
+      RL_STAMP(3)
+      __syncthreads();  // h2, the noise; o_t is copied out
+      RL_STAMP(4)
+      if (wave < MT) {
+        // layer 3 transposed: lane holds row (lane % 16) of its tile, actions 4 g + r; the
+        // argmax of the lane's actions, then one swap with the partner group
+        const int row = wave * 16 + (lane & 15), g = lane >> 4;
+        const uint16_t* hr = L.h2 + row * C::LDH + 8 * g;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < C::S2; ++ks)
+          acc = mfma_step(L.w3[ks * 64 + lane], *reinterpret_cast<const u32x4*>(hr + ks * 32), acc);
+        const f32x4 nz4 = *reinterpret_cast<const f32x4*>(&L.nz[row * 8 + 4 * (g & 1)]);
+        float best_s = -INFINITY;
+        int best_a = 0;
+        f32x4 lg;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int a = 4 * g + r;
+          lg[r] = acc[r] + L.b3[a & 7];
+          const float sc = action_score(lg[r], nz4[r], a < NA);
+          const bool take = (r == 0) | (sc > best_s);
+          best_s = take ? sc : best_s;
+          best_a = take ? a : best_a;
+        }
+        const auto ps = __builtin_amdgcn_permlane16_swap(__float_as_uint(best_s), __float_as_uint(best_s), false, false);
+        const auto pa = __builtin_amdgcn_permlane16_swap((uint32_t)best_a, (uint32_t)best_a, false, false);
+        const float os = __uint_as_float((g & 1) ? ps[0] : ps[1]);
+        const int oa = (int)((g & 1) ? pa[0] : pa[1]);
+        best_a = ((os > best_s) | ((os == best_s) & (oa < best_a))) ? oa : best_a;
+        if (g < 2) *reinterpret_cast<f32x4*>(&L.lg[row * 8 + 4 * g]) = lg;
+        if (g == 0) L.act[row] = best_a;
+      }
+      RL_STAMP(5)
+      __syncthreads();  // actions
+      RL_STAMP(6)
+    }
+    RL_STAMP_END(wave < MT ? 1 : 2)
+    __syncthreads();  // the last observation is painted
+    if (out.obs_last)
+      copy_obs_rows<uint16_t, R, C::D, C::LDX, C::NT>(
+          L.xs, static_cast<uint16_t*>(out.obs_last) + (size_t)e0 * A * C::D, te_valid * A, tid);
+    return;
+  }
+
+  // ------------------------------------------- env wave and helper waves ----
+  const bool envwave = wave == 8;
+  const int el = lane >> 2, q = lane & 3, e = e0 + el;
+  const bool envlane = envwave && el < te_valid;
+  constexpr int nd = 2 * A + 2 * F, nblk = (nd + 7) / 8;
+  auto cl = [&](int c) { return min((uint32_t)c, (uint32_t)HW - 1u); };  // (a malformed state stays inside its row)
+  // (lanes past the agents paint nothing: their row pointer is not used)
+  uint16_t* xr = L.xs + (el * A + min(q, A - 1)) * C::LDX;
+  LbfEnv s{};
+  int fcell2[2] = {0, 0}, flevel2[2] = {0, 0};  // this lane's foods, q and q + 4 (level 0: none)
+  auto own_foods = [&]() {
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+      fcell2[j >> 2] = (j & 3) == q ? s.fcell[j] : fcell2[j >> 2];
+      flevel2[j >> 2] = (j & 3) == q ? s.flevel[j] : flevel2[j >> 2];
+    }
+  };
+  auto paint_foods = [&](bool on) {
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+      xr[HW + cl(s.fcell[j])] =
+          on && !((s.eaten >> j) & 1u) ? small_int_to<uint16_t>((uint32_t)s.flevel[j]) : (uint16_t)0;
+  };
+  auto paint_agents = [&](bool on) {
+    int mc = s.acell[0];
+#pragma unroll
+    for (int i = 1; i < A; ++i) mc = q == i ? s.acell[i] : mc;
+#pragma unroll
+    for (int i = 0; i < A; ++i)
+      xr[cl(s.acell[i])] = on ? small_int_to<uint16_t>((uint32_t)s.alevel[i]) : (uint16_t)0;
+    xr[2 * HW + cl(mc)] = on ? small_int_to<uint16_t>(1u) : (uint16_t)0;
+  };
+  if (envlane) {
+    lbf_load<A, F>(state, p, e, s);
+    own_foods();
+    if (q < A) {
+      paint_foods(true);
+      paint_agents(true);
+    }
+  }
+  // the action draws of step k, one Philox block per row
+  auto draw_words = [&](int k) {
+    if (lane < te_valid * A) {
+      const int re = lane / A, ag = lane - re * A;
+      const Block4 b =
+          draw_block(p.seed, (uint64_t)(p.env_base + e0 + re), t0 + (uint64_t)k, (uint64_t)ag * 256u, TAG_ACTION);
+#pragma unroll
+      for (int w = 0; w < 8; ++w) L.words[lane * 8 + w] = block_u32(b, w);
+    }
+  };
+  auto draw_noise = [&](int i) {
+    if (i < R * NA) {
+      const int r = i / NA, a = i - r * NA;
+      L.nz[r * 8 + a] = gumbel24(L.words[r * 8 + a] >> 8);
+    }
+  };
+  if (wave == 9) draw_words(0);
+  if (envwave) __builtin_amdgcn_s_setprio(3);
+  const int ht = tid - 512;  // helper thread, 0 .. 255
+  RL_STAMP_BEGIN
+  for (int k = 0; k < n_steps; ++k) {
+    const uint64_t t = t0 + (uint64_t)k;
+    uint16_t* og = out.obs ? static_cast<uint16_t*>(out.obs) + ((size_t)k * E + e0) * A * C::D : nullptr;
+    __syncthreads();  // o_t is painted, its action draws made
+    RL_STAMP(0)
+    draw_noise(ht);
+    RL_STAMP(9)
+    if (og) copy_obs_rows<uint16_t, C::CB, C::D, C::LDX, 256>(L.xs, og, te_valid * A, ht);
+    RL_STAMP(10)
+    __syncthreads();  // h1
+    RL_STAMP(2)
+    draw_noise(256 + ht);
+    if (og)
+      copy_obs_rows<uint16_t, R - C::CB, C::D, C::LDX, 256>(L.xs + C::CB * C::LDX, og + (size_t)C::CB * C::D,
+                                                            te_valid * A - C::CB, ht);
+    RL_STAMP(10)
+    __syncthreads();  // h2, the noise; o_t is copied out
+    RL_STAMP(4)
+    __syncthreads();  // actions
+    RL_STAMP(6)
+    if (envwave) {
+      // ---- the quad's step (rules: lbf_transition_rc) ----
+      const int aq = q < A ? L.act[min(el * A + q, R - 1)] : 0;
+      int act[A];
+      act[0] = __builtin_amdgcn_mov_dpp(aq, 0x00, 0xf, 0xf, false);
+      if constexpr (A > 1) act[1] = __builtin_amdgcn_mov_dpp(aq, 0x55, 0xf, 0xf, false);
+      if constexpr (A > 2) act[2] = __builtin_amdgcn_mov_dpp(aq, 0xaa, 0xf, 0xf, false);
+      if constexpr (A > 3) act[3] = __builtin_amdgcn_mov_dpp(aq, 0xff, 0xf, 0xf, false);
+      int ar[A], ac[A];
+#pragma unroll
+      for (int i = 0; i < A; ++i) {
+        ar[i] = (int)((uint32_t)s.acell[i] / (uint32_t)GW);
+        ac[i] = s.acell[i] - ar[i] * GW;
+      }
+      int mr = ar[0], mc = ac[0];
+#pragma unroll
+      for (int i = 1; i < A; ++i) {
+        mr = q == i ? ar[i] : mr;
+        mc = q == i ? ac[i] : mc;
+      }
+      const int r2 = mr + (aq == 1 ? -1 : aq == 2 ? 1 : 0), c2 = mc + (aq == 3 ? -1 : aq == 4 ? 1 : 0);
+      const int cell = r2 * GW + c2;
+      bool ok = (q < A) & (aq >= 1) & (aq <= 4) & (r2 >= 0) & (r2 < GH) & (c2 >= 0) & (c2 < GW);
+#pragma unroll
+      for (int j = 0; j < F; ++j) ok &= !(!((s.eaten >> j) & 1u) & (s.fcell[j] == cell));
+#pragma unroll
+      for (int i = 0; i < A; ++i) ok &= s.acell[i] != cell;
+      const int mytgt = ok ? cell : -1;
+      int tgt[A];
+      tgt[0] = __builtin_amdgcn_mov_dpp(mytgt, 0x00, 0xf, 0xf, false);
+      if constexpr (A > 1) tgt[1] = __builtin_amdgcn_mov_dpp(mytgt, 0x55, 0xf, 0xf, false);
+      if constexpr (A > 2) tgt[2] = __builtin_amdgcn_mov_dpp(mytgt, 0xaa, 0xf, 0xf, false);
+      if constexpr (A > 3) tgt[3] = __builtin_amdgcn_mov_dpp(mytgt, 0xff, 0xf, 0xf, false);
+      // this lane's foods against the loaders' pre-step cells
+      uint32_t got = 0;
+      int got_sum = 0;
+#pragma unroll
+      for (int h = 0; h < (F + 3) / 4; ++h) {
+        const int fr = (int)((uint32_t)fcell2[h] / (uint32_t)GW), fc = fcell2[h] - fr * GW, j = q + 4 * h;
+        int lsum = 0;
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+          lsum += ((act[i] == 5) & (abs(ar[i] - fr) + abs(ac[i] - fc) == 1)) ? s.alevel[i] : 0;
+        const bool eat = (j < F) & !((s.eaten >> j) & 1u) & (lsum > 0) & (lsum >= flevel2[h]);
+        got |= eat ? (1u << j) : 0u;
+        got_sum += eat ? flevel2[h] : 0;
+      }
+      got |= (uint32_t)__builtin_amdgcn_mov_dpp((int)got, 0xb1, 0xf, 0xf, false);  // quad_perm [1,0,3,2]
+      got |= (uint32_t)__builtin_amdgcn_mov_dpp((int)got, 0x4e, 0xf, 0xf, false);  // quad_perm [2,3,0,1]
+      got_sum += __builtin_amdgcn_mov_dpp(got_sum, 0xb1, 0xf, 0xf, false);
+      got_sum += __builtin_amdgcn_mov_dpp(got_sum, 0x4e, 0xf, 0xf, false);
+      RL_STAMP(7)
+      if (envlane && q < A) paint_agents(false);
+      int newcell[LBF_MAXA] = {s.acell[0], s.acell[1], s.acell[2], s.acell[3]};
+#pragma unroll
+      for (int i = 0; i < A; ++i) {
+        bool contested = false;
+#pragma unroll
+        for (int k2 = 0; k2 < A; ++k2)
+          if (k2 != i) contested |= tgt[k2] == tgt[i];
+        newcell[i] = ((tgt[i] >= 0) & !contested) ? tgt[i] : s.acell[i];
+      }
+      float r;
+      uint32_t d;
+      lbf_finish<F>(p, s, newcell, s.eaten | got, got_sum, r, d);
+      d = envlane ? d : 0u;
+      const uint64_t done_mask = __ballot(d != 0);
+      const bool changed = got != 0 || d != 0;
+      if (done_mask) {  // reset blocks of every env that ended, one Philox block per lane
+        const int j = lane / nblk, blk = lane - j * nblk;
+        if (j < TE && ((done_mask >> (j * 4)) & 1ull)) {
+          const Block4 b = draw_block(p.seed, (uint64_t)(p.env_base + e0 + j), t + 1, (uint64_t)blk, TAG_RESET);
+#pragma unroll
+          for (int w = 0; w < 8; ++w)
+            if (blk * 8 + w < LBF_MAX_DRAWS) L.rdraw[j * LBF_MAX_DRAWS + blk * 8 + w] = block_u32(b, w);
+        }
+        wave_lds_sync();
+        if (d) {
+          if (q < A) paint_foods(false);
+          uint32_t dw[LBF_MAX_DRAWS];
+#pragma unroll
+          for (int w = 0; w < LBF_MAX_DRAWS; ++w) dw[w] = w < nd ? L.rdraw[el * LBF_MAX_DRAWS + w] : 0u;
+          lbf_reset_from_draws<A, F>(p, dw, s);
+          own_foods();
+        }
+      }
+      if (envlane && q < A) {
+        if (changed) paint_foods(true);
+        paint_agents(true);
+      }
+      if (envlane && q == 0) {
+        if (out.reward) out.reward[(size_t)k * E + e] = r;
+        if (out.done) out.done[(size_t)k * E + e] = (uint8_t)d;
+      }
+      RL_STAMP(8)
+    } else {
+      const int j = tid - 576;  // 0 .. 191
+      for (int i = j; i < te_valid * A * NA; i += 192)
+        if (out.logits) out.logits[((size_t)k * E + e0) * A * NA + i] = L.lg[(i / NA) * 8 + i % NA];
+      if (out.actions && j < te_valid * A) out.actions[((size_t)k * E + e0) * A + j] = L.act[j];
+      if (wave == 9 && k + 1 < n_steps) draw_words(k + 1);
+      RL_STAMP(8)
+    }
+  }
+  RL_STAMP_END(envwave ? 0 : 3)
+  __syncthreads();  // the last observation is painted
+  if (out.obs_last)
+    copy_obs_rows<uint16_t, R, C::D, C::LDX, C::NT>(
+        L.xs, static_cast<uint16_t*>(out.obs_last) + (size_t)e0 * A * C::D, te_valid * A, tid);
+  if (envlane && q == 0) lbf_store<A, F>(state, p, e, s);
+}
+
+template <int GH, int GW, int A, int F>
+static hipError_t launch_run_fs(const LbfParams& p, const PolicyArgs& pol, int32_t* state, uint64_t t0, int n_steps,
+                                const TrajArgs& out, hipStream_t s) {
+  using C = LbfFs<GH, GW, A, F>;
+  const hipError_t e = hipFuncSetAttribute((const void*)lbf_run_fs_kernel<GH, GW, A, F>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(typename C::Lds));
+  if (e != hipSuccess) return e;
+  lbf_run_fs_kernel<GH, GW, A, F><<<dim3((unsigned)((p.E + C::TE - 1) / C::TE)), C::NT, sizeof(typename C::Lds), s>>>(
+      p, pol, state, t0, n_steps, out);
+  return hipGetLastError();
+}
+
 // Compile-time shapes that run on lbf_rollout_kernel (everything else uses
 // lbf_run_kernel): LBF 8x8 with 2 agents and 3 foods (obs 192) under 64- and
 // 128-wide layers.
-template <int DT, int GH, int GW, int H1, int H2, int A, int F, int TE, int NW, int MINB, bool VH, bool TM,
-          bool S1 = false>
+template <int DT, int GH, int GW, int H1, int H2, int A, int F, int TE, int NW, int MINB, bool VH, bool TM>
 static hipError_t launch_rollout_reg(const LbfParams& p, const LbfMagic&, const PolicyArgs& pol, int32_t* state,
                                      uint64_t t0, int n_steps, const TrajArgs& out, hipStream_t s) {
-  auto kern = lbf_rollout_kernel<DT, GH, GW, H1, H2, LBF_NACT, A, F, TE, NW, MINB, VH, TM, S1>;
+  auto kern = lbf_rollout_kernel<DT, GH, GW, H1, H2, LBF_NACT, A, F, TE, NW, MINB, VH, TM>;
   const dim3 grid((unsigned)((p.E + TE - 1) / TE));
   kern<<<grid, NW * 64, 0, s>>>(p, pol, state, t0, n_steps, out);
   return hipGetLastError();
@@ -1263,14 +1672,14 @@ static bool try_launch_rollout_reg(const LbfParams& p, const LbfMagic& m, const 
   RL_REG_CASE(DT_BF16, 8, 8, 128, 128, 2, 3, 8, 4, 2, 0)
   if (pol.dt == DT_BF16 && p.H == 12 && p.W == 12 && pol.H1 == 256 && pol.H2 == 256 && p.A == 3 && p.F == 6 &&
       !pol.VH && !tm) {
-    // layer 1 (432 x 256) streamed from the packed copy: both layers resident
-    // spill; without a packed copy they stay resident all the same
+    // with a packed copy: layer 1 streamed, the step split over waves by role
+    // (16384 envs x 128 steps 2.93 ms; layers 1 and 2 run by all waves in turn with the
+    // env step, 4.08 ms); without one both layers stay in registers and spill
     if (pol.Wp[0] != nullptr)
-      *err = launch_rollout_reg<DT_BF16, 12, 12, 256, 256, 3, 6, 16, 8, 1, false, false, true>(p, m, pol, state, t0,
-                                                                                            n_steps, out, s);
+      *err = launch_run_fs<12, 12, 3, 6>(p, pol, state, t0, n_steps, out, s);
     else
-      *err = launch_rollout_reg<DT_BF16, 12, 12, 256, 256, 3, 6, 16, 8, 1, false, false, false>(p, m, pol, state, t0,
-                                                                                             n_steps, out, s);
+      *err = launch_rollout_reg<DT_BF16, 12, 12, 256, 256, 3, 6, 16, 8, 1, false, false>(p, m, pol, state, t0, n_steps,
+                                                                                     out, s);
     return true;
   }
   RL_REG_CASE(DT_BF16, 7, 7, 128, 128, 2, 3, 8, 4, 2, 0)

@@ -126,6 +126,40 @@ def test_kitchen_role_split_rollout(E, keep):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("E", [1, 15, 17, 40])
+@pytest.mark.parametrize("keep", [("obs", "actions", "logits", "reward", "done", "obs_last"), ("reward",), ("obs_last",)])
+def test_lbf12_role_split_rollout(E, keep):
+    """256-wide packed 12x12 policies run on a kernel of their own (a quad of lanes per env): ragged tiles of 16
+    envs, foods eaten and episodes ended inside the launch, a launch split in two and outputs left out give the
+    unpacked (register-resident) kernel's results, bit for bit."""
+    require_gpu()
+    _note(f"12x12 role-split rollout E={E} keep={keep}")
+    ws, bs = workloads.policy_weights((432, 256, 256, 6), seed=33, bias_scale=0.3)
+    bs[2][5] += 2.0  # load often
+    cfg = R.EnvConfig(n_envs=E, env_base=91, seed=6, **dict(workloads.WORKLOADS["lbf12_16k"]["env"], max_steps=23,
+                                                             max_food_level=1))
+    res = []
+    for pack in (True, False):
+        pol = R.Policy(ws, bs, "bf16", pack=pack)
+        state = R.new_state(cfg)
+        R.rollout_init(cfg, state)
+        got = []
+        for t0, T in ((0, 41), (41, 1), (42, 30)):
+            out = dict(obs=torch.empty(T, E, 3, 432, dtype=torch.bfloat16, device="cuda"),
+                       actions=torch.empty(T, E, 3, dtype=torch.int32, device="cuda"),
+                       logits=torch.empty(T, E, 3, 6, device="cuda"), reward=torch.empty(T, E, device="cuda"),
+                       done=torch.empty(T, E, dtype=torch.uint8, device="cuda"),
+                       obs_last=torch.empty(E, 3, 432, dtype=torch.bfloat16, device="cuda"))
+            out = {k: v for k, v in out.items() if k in keep}
+            R.rollout_run(cfg, pol, state, t0, T, **out)
+            got += [out[k].cpu() for k in keep] + [state.cpu().clone()]
+        if "reward" in keep and E > 1:
+            assert any(bool((g > 0).any()) for g in got if g.dtype == torch.float32)  # foods are eaten
+        res.append(got)
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dims", [(432, 256, 256, 6), (658, 512, 512, 20), (1170, 256, 256, 6), (300, 512, 32, 20)])
 def test_packed_policy_forward_equals_unpacked(dims):
     """The tiled policy forward stages its weight slices from the packed copy: same logits, bit for bit."""
