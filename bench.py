@@ -553,10 +553,10 @@ PHASE_CASES = (
       5: "layer 3 + Gumbel argmax", 6: "barrier", 7: "transition (env lanes)",
       8: "repaint o_t+1 (env lanes) / actions and logits out (helpers)", 9: "Gumbel noise",
       10: "copy o_t to the trajectory"}),
-    ("Hanabi fused rollout", "hn_4096", "run", "hn", 0, ("all waves",),
-     {0: "barrier at the step's top", 1: "observation bit vectors", 2: "paint layer-1 tile", 3: "layer 1",
-      4: "layer 2", 5: "layer 3", 6: "legal mask + Gumbel scores", 7: "copy o_t to the trajectory",
-      8: "argmax + transition", 9: "re-deals"}),
+    ("Hanabi fused rollout", "hn_4096", "run", "hn", 0, ("env wave", "MLP waves", "helper waves"),
+     {0: "barrier at the step's top", 1: "layer 1", 2: "barrier", 3: "layer 2 (MLP) / Gumbel noise (env wave) / o_t to the trajectory (helpers)", 4: "barrier",
+      5: "layer 3 + Gumbel argmax", 6: "barrier", 7: "movers' bit vectors (MLP) / outputs (env wave)",
+      8: "move, deal, publish", 9: "decks, second half (helpers)", 10: "Gumbel noise (env wave) / decks, other players' bit vectors (helpers)"}),
 )
 
 

@@ -29,6 +29,7 @@ struct HnGame {
   static constexpr int PER_COLOUR = 3 + 2 * (R - 2) + 1;
   static constexpr int CARDS = C * PER_COLOUR, KINDS = C * R, NACT = 2 * H + C + R;
   static constexpr int DW = (CARDS + 3) / 4;  // deck words in use
+  static constexpr int NB = (CARDS - 1 + 7) / 8;  // Philox blocks of a shuffle
   static constexpr int LASTW = 2 + 4 + 2 + C + R + H + H + KINDS + 1 + 1;
   // observation sections, in order
   static constexpr int O_FLAGS = H * KINDS, O_DECK = O_FLAGS + 2, O_FW = O_DECK + CARDS - 2 * H,
@@ -115,9 +116,8 @@ __device__ __forceinline__ void hn_add_disc(HnEnv& s, int card) {
 // the game's deck are 0): lane 4 w holds word w.
 template <class G>
 __device__ __forceinline__ uint32_t hn_wave_deck(uint64_t seed, uint64_t env, uint64_t t, int lane) {
-  constexpr int NB = (G::CARDS - 1 + 7) / 8;
   Block4 b{0, 0, 0, 0};
-  if (lane < NB) b = draw_block(seed, env, t, (uint64_t)lane, TAG_RESET);
+  if (lane < G::NB) b = draw_block(seed, env, t, (uint64_t)lane, TAG_RESET);
   int x = lane;
 #pragma unroll
   for (int i = 1; i < G::CARDS; ++i) {
@@ -231,10 +231,12 @@ __device__ __forceinline__ void hn_orient(HnEnv& s, bool sw) {
 
 // One move of the player to move (an illegal or out-of-range action acts as
 // its lowest legal one); `s` becomes the post-transition state (no reset).
-template <class G>
-__device__ __forceinline__ void hn_transition(const HnParams& p, HnEnv& s, int a_in, float& reward, uint32_t& done) {
+// `legal` is hn_legal(s), next_card() the card that hn_deck_card(s, s.next)
+// gives (callers that know them ahead of the action pass them in).
+template <class G, class NextCard>
+__device__ __forceinline__ void hn_transition(const HnParams& p, HnEnv& s, int a_in, float& reward, uint32_t& done,
+                                              uint32_t legal, NextCard next_card) {
   constexpr int HN_HAND = G::H, HN_RANKS = G::R, HN_COLOURS = G::C, HN_CARDS = G::CARDS, HN_NACT = G::NACT;
-  const uint32_t legal = hn_legal<G>(s);
   const int a = ((unsigned)a_in < (unsigned)HN_NACT && ((legal >> a_in) & 1u)) ? a_in : __builtin_ctz(legal);
   const int mover = s.cur;
   hn_orient(s, mover == 1);
@@ -277,7 +279,7 @@ __device__ __forceinline__ void hn_transition(const HnParams& p, HnEnv& s, int a
     s.n[pl] -= 1;
     if (s.next < HN_CARDS) {
       const int sh = 5 * s.n[pl];
-      s.hand[pl] |= (uint32_t)hn_deck_card(s, s.next) << sh;
+      s.hand[pl] |= (uint32_t)next_card() << sh;
       s.kc[pl] |= ((1u << HN_COLOURS) - 1u) << sh;
       s.kr[pl] |= ((1u << HN_RANKS) - 1u) << sh;
       s.n[pl] += 1;
@@ -328,6 +330,11 @@ __device__ __forceinline__ void hn_transition(const HnParams& p, HnEnv& s, int a
   s.steps += 1;
   reward = (float)rew;
   done = (terminated ? 1u : 0u) | (s.steps >= p.max_steps ? 2u : 0u);
+}
+
+template <class G>
+__device__ __forceinline__ void hn_transition(const HnParams& p, HnEnv& s, int a_in, float& reward, uint32_t& done) {
+  hn_transition<G>(p, s, a_in, reward, done, hn_legal<G>(s), [&]() { return hn_deck_card(s, s.next); });
 }
 
 // State planes (int32, E entries each); see include/rollout.h.
@@ -387,8 +394,8 @@ __device__ __forceinline__ void hn_store(int32_t* __restrict__ st, int E, int e,
 constexpr int HN_OBS_WORDS = (HN_OBS + 63) / 64;  // (the largest game)
 constexpr int HN_NFIELDS = HnStd::NFIELDS;
 
-// What the field computations read of one game (published to LDS after each move).
-struct HnPub {
+// What the field computations read of one game (published to LDS after each move, in 16-byte writes).
+struct alignas(16) HnPub {
   uint32_t hand[2], kc[2], kr[2], hc[2], hr[2];
   int n[2];
   uint32_t fw, disc0, disc1, last;

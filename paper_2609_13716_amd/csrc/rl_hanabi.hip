@@ -167,14 +167,14 @@ struct HnExpand {
 
 // Write a tile's `total` observation features, held in the flat layout
 // (from bit 0 of `bytes`), to consecutive global elements from `dst` as
-// 0 / 1 values, and clear the bytes written out.  Wave w of the NW taking
+// 0 / 1 values, and clear the bytes written out (CLEAR).  Wave w of the NW taking
 // part writes its share, a contiguous run of whole 16-byte vectors (or of
 // 4-byte words when `dst` is not 16-byte aligned or `total` is not a whole
 // number of vectors) that starts and ends on a byte of the bit array, so no
 // two waves clear the same byte.  Per vector: one LDS byte (or nibble) read
 // and one table read, in batches of up to eight whose reads are all issued
 // before their stores.
-template <class G, typename OT, int MAXF, int NW>
+template <class G, typename OT, int MAXF, int NW, bool CLEAR = true>
 __device__ __forceinline__ void hn_write_flat(uint8_t* bytes, int total, OT* __restrict__ dst, int w, int lane,
                                               const u32x4* lut) {
   constexpr int VE = 16 / sizeof(OT), WE = 4 / sizeof(OT);  // features per 16-byte vector, per word
@@ -206,6 +206,7 @@ __device__ __forceinline__ void hn_write_flat(uint8_t* bytes, int total, OT* __r
         if (i0 + it < IT && v < v1) g4[v] = val[it];
       }
     }
+    if constexpr (!CLEAR) return;
     wave_lds_sync();
     for (int j = v0 / VB + lane; j < (v1 + VB - 1) / VB; j += 64) bytes[j] = 0;
   } else {
@@ -218,6 +219,7 @@ __device__ __forceinline__ void hn_write_flat(uint8_t* bytes, int total, OT* __r
       const uint32_t bb = ((uint32_t)bytes[f >> 3] >> (f & 7)) & ((1u << WE) - 1u);
       g[x] = lut[bb][0];  // (entry bb's first word holds features 0 .. WE-1 of bb)
     }
+    if constexpr (!CLEAR) return;
     wave_lds_sync();
     for (int j = w0 / WB + lane; j < (w1 + WB - 1) / WB; j += 64) bytes[j] = 0;
   }
@@ -656,6 +658,487 @@ __global__ __launch_bounds__(HN_RUN_NT) void hn_run_kernel(HnParams p, PolicyArg
   if (envlane) hn_store(state, E, e, s);
 }
 
+// ------------------- fused rollout, 256- and 512-wide packed bf16 policies ----
+//
+// The rollout of hn_run_kernel for OBS-H-H-NACT policies in the packed layout,
+// with the work of a step split over 12 waves by role, so that little but the
+// weight stream and the env wave's chain is on a step's critical path:
+//   waves 0-7   the MLP: H / 128 unit tiles each of layers 1 and 2.  Part of layer
+//               2's weights stay in registers for the whole rollout (R2 K steps),
+//               part of layer 1's in LDS (LK K steps), the rest streams from L2
+//               through one ring of P K steps that runs through both layers and on
+//               into the next step's layer 1, so it fills while the games move.
+//               Layer 1 reads its row operands straight from the observation bit
+//               vectors: the 8 features of an operand are one byte, expanded through
+//               the trajectory's 256-entry table.  These waves store nothing to
+//               global memory: a load waits for its wave's earlier stores.
+//   wave 8      the env wave: layer 3 (weights in LDS) and the Gumbel argmax, whose
+//               lanes 16 g + r all end with row r's action and all hold game r, so
+//               the move, the deal and the publishing follow without a barrier.
+//               Under layers 1 and 2 it draws the step's noise.
+//   waves 9-11  under layers 1 and 2: the decks of the games that the coming move may
+//               end (a re-deal depends only on the env and the step; wave 9, in the
+//               standard game wave 10 too); under layer 1: the other player's bit vectors
+//               (the other waves); under layer 2: o_t to the trajectory.
+//   waves 0-6   the next movers' bit vectors once the games are published.
+// Every layer's sums run over K in the order of hn_run_kernel: same bits.
+//
+// What bounds it: 512-wide, the weight stream.  32 of the 37 K steps (1 MB) pass the
+// CU's path to L2 every step at 45-52 bytes per clock: about 21,000 of a step's 29,000
+// cycles; then the env wave's chain (layer 3 2,400, move and deal 2,500, the movers'
+// bit vectors 1,400).  256-wide, where most weights stay on chip, that chain and the
+// Philox and float64 work of waves 8-11.  Measured, 4096 games x 80 steps: 1.53 ms on
+// hn_run_kernel (every wave streams all the weights, then takes part in the other work),
+// 0.98 ms here; the 3 x 3 game at 256 0.78 and 0.46 ms; 64 games 1.54 and 0.92 ms; 16384
+// games x 20 steps 1.59 and 1.00 ms.  Tried: ring and resident K steps (P, R2) of (3, 2) 0.98, (4, 3)
+// 1.10 (spills); one wave-wide shuffle per flagged game (1.14; the byte swaps take one
+// lane per game); waves 9-11 at the MLP waves' priority (1.11 against 1.06: the older
+// MLP waves go first at the memory pipe); one loop for the env and helper waves (1.05,
+// the game's registers spill around the copy); o_t copied straight from the gapped rows
+// (three LDS words per vector) or partly by the env wave (1.13).
+template <class G, int H>
+struct HnFs {
+  static constexpr int TPW = H / 128;                    // unit tiles per MLP wave
+  static constexpr int S1 = (G::OBS + 31) / 32, S2 = H / 32;  // K steps
+  // K steps held on chip: LK of layer 1 (the last ones, LDS), R2 of layer 2 (the last ones, registers)
+  static constexpr int LK = H == 512 ? 2 : 5, R2 = H == 512 ? 3 : S2;
+  static constexpr int P = H == 512 ? 2 : 4;            // streamed K steps in flight
+  static constexpr int N1 = S1 - LK, NS = N1 + S2 - R2;  // streamed K steps: layer 1's, both layers'
+  static_assert(NS % P == 0 && NS >= P, "a step's stream ends where the ring begins");
+  static constexpr int LD = H + 8;
+  static constexpr int NT3 = (G::NACT + 15) / 16;        // layer 3's tiles
+};
+constexpr int HN_FS_NT = 768;
+constexpr int HN_FS_ROWS = 12;  // rows of o_t that each of waves 9-11 copies (whole 16-byte vectors in four rows)
+static_assert(3 * HN_FS_ROWS >= 2 * HN_RUN_TE && HN_FS_ROWS % 4 == 0, "all rows, aligned");
+
+template <class G, int H>
+struct HnFsLds {
+  using F = HnFs<G, H>;
+  uint64_t bits[2 * HN_RUN_TE][HN_OBS_WORDS];  // o_t, row 2 el + player; zero between o_t's copy and the move
+  u32x4 lut[256];
+  uint16_t h1[HN_RUN_TE * F::LD], h2[HN_RUN_TE * F::LD];
+  u32x4 w1[F::LK * (H / 16) * 64];             // layer-1 operands of the last K steps: (step, tile, lane)
+  u32x4 w3[F::NT3 * F::S2 * 64];               // layer-3 operands: (tile, step, lane)
+  float bias[2 * H];
+  uint32_t draws[HN_RUN_TE * 24];              // the env wave's: random words of the step's noise, by (game, action)
+  float nz[HN_RUN_TE * 32];                    // the env wave's: the step's Gumbel noise, by (game, action)
+  uint32_t flat[3][(HN_FS_ROWS * G::OBS + 31) / 32];  // each copying wave's rows of o_t without gaps
+  HnPub pub[HN_RUN_TE];                        // the games as of the last move
+  uint32_t words[HN_RUN_TE][HN_DECK_WORDS];    // decks drawn for the games flagged in may_end
+  uint32_t may_end[HN_RUN_TE];
+  uint32_t order[HN_DECK_WORDS];               // the ordered deck
+  uint32_t swaps[HN_RUN_TE][16];               // the deck wave's: swap positions, byte k of a game's draw k
+};
+
+// Whether the next move can end the game (a superset of hn_transition's done):
+// no or one life left, the last turn, at most one firework card missing, the step limit.
+template <class G>
+__device__ __forceinline__ bool hn_may_end(const HnParams& p, const HnEnv& s) {
+  int played = 0;
+#pragma unroll
+  for (int c = 0; c < G::C; ++c) played += (int)hn_field(s.fw, 3, c);
+  return (s.lives <= 1) | (s.turns_left == 0) | (s.turns_left == 1) | (played >= G::C * G::R - 1) |
+         (s.steps + 1 >= p.max_steps);
+}
+
+template <class G, int H>
+__global__ __launch_bounds__(HN_FS_NT) void hn_run_fs_kernel(HnParams p, PolicyArgs pol, int32_t* __restrict__ state,
+                                                           uint64_t t0, int n_steps, TrajArgs out) {
+  using F = HnFs<G, H>;
+  constexpr int TE = HN_RUN_TE, NA = G::NACT, TPW = F::TPW, S1 = F::S1, S2 = F::S2, LK = F::LK, R2 = F::R2,
+                P = F::P, N1 = F::N1, NS = F::NS, LD = F::LD, NT3 = F::NT3;
+  extern __shared__ __align__(16) uint8_t smem[];
+  HnFsLds<G, H>& L = *reinterpret_cast<HnFsLds<G, H>*>(smem);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int e0 = blockIdx.x * TE, te_valid = min(TE, p.E - e0), E = p.E;
+  const uint16_t* Wp1 = static_cast<const uint16_t*>(pol.Wp[0]);
+  const uint16_t* Wp2 = static_cast<const uint16_t*>(pol.Wp[1]);
+  const uint16_t* Wp3 = static_cast<const uint16_t*>(pol.Wp[2]);
+  auto block = [](const uint16_t* Wp, int S, int tile, int ks, int ln) {
+    return *reinterpret_cast<const u32x4*>(Wp + ((size_t)(tile * S + ks) * 64 + ln) * 8);
+  };
+  zero_lds<HN_FS_NT>(smem, sizeof(L), tid);
+  __syncthreads();
+  for (int i = tid; i < LK * (H / 16) * 64; i += HN_FS_NT) {
+    const int q = i / (H / 16 * 64), r = i - q * (H / 16 * 64);
+    L.w1[i] = block(Wp1, S1, r >> 6, N1 + q, r & 63);
+  }
+  for (int i = tid; i < NT3 * S2 * 64; i += HN_FS_NT) L.w3[i] = block(Wp3, S2, 0, i >> 6, i & 63);
+  for (int i = tid; i < 2 * H; i += HN_FS_NT)
+    L.bias[i] = bf16_to_f32(i < H ? static_cast<const uint16_t*>(pol.b[0])[i]
+                                  : static_cast<const uint16_t*>(pol.b[1])[i - H]);
+  for (int i = tid; i < 256; i += HN_FS_NT) L.lut[i] = HnExpand<uint16_t>::entry((uint32_t)i);
+  if (tid < G::CARDS) {
+    const int c = tid / G::PER_COLOUR, o = tid - c * G::PER_COLOUR;
+    reinterpret_cast<uint8_t*>(L.order)[tid] = (uint8_t)(c * G::R + (o < 3 ? 0 : min((o - 3) / 2 + 1, G::R - 1)));
+  }
+  // bit vectors of one row per game (the mover's, or the other player's) by threads i0, i0 + stride, ...
+  auto build_rows = [&](bool movers, int i0, int stride) {
+    for (int i = i0; i < TE * G::NFIELDS; i += stride) {
+      const int f = i / TE, el = i - f * TE;
+      if (el >= te_valid) continue;
+      const HnPub& v = L.pub[el];
+      const int me = movers ? v.cur : 1 - v.cur;
+      int off;
+      const uint64_t b = hn_field_bits<G>(v, me, f, off);
+      if (b) {
+        unsigned long long* w = reinterpret_cast<unsigned long long*>(L.bits[2 * el + me]);
+        const int j = off >> 6, sh = off & 63;
+        atomicOr(w + j, (unsigned long long)(b << sh));
+        if (sh && (b >> (64 - sh))) atomicOr(w + j + 1, (unsigned long long)(b >> (64 - sh)));
+      }
+    }
+  };
+
+  if (wave < 8) {
+    // ------------------------------------------------------------- MLP ----
+    u32x4 w2[R2][TPW], ring[P][TPW];
+#pragma unroll
+    for (int q = 0; q < R2; ++q)
+#pragma unroll
+      for (int o = 0; o < TPW; ++o) w2[q][o] = block(Wp2, S2, TPW * wave + o, S2 - R2 + q, lane);
+    // streamed K step s (layer 1's first, then layer 2's) of every owned tile to a ring slot; the base is opaque, so
+    // that the addresses of a step's loads are not all formed ahead of the step loop and spilled
+    auto fetch = [&](int s, u32x4 (&dst)[TPW]) {
+      const uint16_t* w = (s < N1 ? Wp1 + (size_t)(TPW * wave * S1 + s) * 512
+                                  : Wp2 + (size_t)(TPW * wave * S2 + s - N1) * 512);
+      asm volatile("" : "+s"(w));
+#pragma unroll
+      for (int o = 0; o < TPW; ++o)
+        dst[o] = *reinterpret_cast<const u32x4*>(w + (size_t)o * (s < N1 ? S1 : S2) * 512 + 8 * lane);
+    };
+#pragma unroll
+    for (int q = 0; q < P; ++q) fetch(q, ring[q]);
+    // one streamed K step: its MFMAs, its ring slots refilled (a stream that fits the ring stays there)
+    auto step = [&](int s, u32x4 a, f32x4 (&acc)[TPW]) {
+#pragma unroll
+      for (int o = 0; o < TPW; ++o) acc[o] = mfma_step(ring[s % P][o], a, acc[o]);
+      if constexpr (NS > P) fetch((s + P) % NS, ring[s % P]);
+    };
+    // tanh(acc + bias) of each owned tile: four consecutive units of one row per lane
+    auto store_tanh = [&](const f32x4 (&acc)[TPW], const float* bias, uint16_t* dst) {
+#pragma unroll
+      for (int o = 0; o < TPW; ++o) {
+        const int u0 = (TPW * wave + o) * 16 + 4 * (lane >> 4);
+        const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + u0);
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fast_tanh(acc[o][r] + b4[r]);
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<u32x2*>(dst + (lane & 15) * LD + u0) =
+            u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      }
+    };
+    const uint16_t* h1row = L.h1 + (lane & 15) * LD + 8 * (lane >> 4);
+    __syncthreads();  // the games are published
+    if (wave < 7) build_rows(true, tid, 448);
+    RL_STAMP_BEGIN
+    for (int k = 0; k < n_steps; ++k) {
+      __syncthreads();  // the movers' bit vectors
+      RL_STAMP(0)
+      {
+        const uint8_t* xb = reinterpret_cast<const uint8_t*>(L.bits[2 * (lane & 15) + L.pub[lane & 15].cur]) + (lane >> 4);
+        f32x4 acc[TPW];
+#pragma unroll
+        for (int o = 0; o < TPW; ++o) acc[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+        uint32_t b[2];  // feature bytes of K steps ks + 1, ks + 2
+        u32x4 a[2];     // row operands of K steps ks, ks + 1
+        b[0] = xb[0];
+        b[1] = xb[4];
+        a[0] = L.lut[b[0]];
+        b[0] = xb[8];
+#pragma unroll
+        for (int ks = 0; ks < S1; ++ks) {
+          if (ks + 1 < S1) a[(ks + 1) & 1] = L.lut[b[(ks + 1) & 1]];
+          if (ks + 3 < S1) b[(ks + 1) & 1] = xb[4 * (ks + 3)];
+          if (ks < N1) {
+            __builtin_amdgcn_sched_barrier(0);
+            step(ks, a[ks & 1], acc);
+          } else {
+            u32x4 w[TPW];
+#pragma unroll
+            for (int o = 0; o < TPW; ++o) w[o] = L.w1[((ks - N1) * (H / 16) + TPW * wave + o) * 64 + lane];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int o = 0; o < TPW; ++o) acc[o] = mfma_step(w[o], a[ks & 1], acc[o]);
+          }
+        }
+        store_tanh(acc, L.bias, L.h1);
+      }
+      RL_STAMP(1)
+      __syncthreads();  // h1, the other rows' bit vectors, the noise
+      RL_STAMP(2)
+      {
+        f32x4 acc[TPW];
+#pragma unroll
+        for (int o = 0; o < TPW; ++o) acc[o] = f32x4{0.f, 0.f, 0.f, 0.f};
+        u32x4 a[2];
+        a[0] = *reinterpret_cast<const u32x4*>(h1row);
+#pragma unroll
+        for (int ks = 0; ks < S2; ++ks) {
+          if (ks + 1 < S2) a[(ks + 1) & 1] = *reinterpret_cast<const u32x4*>(h1row + (ks + 1) * 32);
+          __builtin_amdgcn_sched_barrier(0);
+          if (ks < S2 - R2) {
+            step(N1 + ks, a[ks & 1], acc);
+          } else {
+#pragma unroll
+            for (int o = 0; o < TPW; ++o) acc[o] = mfma_step(w2[ks - (S2 - R2)][o], a[ks & 1], acc[o]);
+          }
+        }
+        store_tanh(acc, L.bias + H, L.h2);
+      }
+      RL_STAMP(3)
+      __syncthreads();  // h2; o_t is copied out and its bit vectors are clear; the decks
+      RL_STAMP(4)
+      __syncthreads();  // the games are published
+      RL_STAMP(6)
+      if (wave < 7) build_rows(true, tid, 448);
+      RL_STAMP(7)
+    }
+    RL_STAMP_END(1)
+    if (out.obs_last) {
+      __syncthreads();  // both rows' bit vectors
+      if (wave < 4) {
+        const int r0 = 8 * wave, nr = min(8, 2 * te_valid - r0);
+        if (nr > 0)
+          hn_write_obs<G, uint16_t, 8>(L.bits[r0], nr,
+                                       static_cast<uint16_t*>(out.obs_last) + ((size_t)e0 * 2 + r0) * G::OBS, lane, L.lut);
+      }
+    }
+    return;
+  }
+
+  if (wave == 8) {
+    // -------------------------------------------------------- env wave ----
+    const int row = lane & 15, g = lane >> 4, e = e0 + min(row, te_valid - 1);
+    const bool owner = lane < te_valid;  // the lane that stores its game
+    HnEnv s;
+    hn_load(state, E, e, s);  // lanes 16 g + r hold game r
+    float b3[NT3][4];
+#pragma unroll
+    for (int j = 0; j < NT3; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int a = 16 * j + 4 * g + r;
+        b3[j][r] = a < NA ? bf16_to_f32(static_cast<const uint16_t*>(pol.b[2])[a]) : 0.f;
+      }
+    auto publish = [&]() {
+      if (owner) {
+        hn_pub(s, L.pub[row]);
+        L.may_end[row] = hn_may_end<G>(p, s) ? 1u : 0u;
+      }
+    };
+    // The step's noise, one action of each lane per pass: passes 0-3 its four actions of
+    // layer 3's first tile, pass 4 one of the second tile's four (NACT <= 20).
+    constexpr int NBLK = (NA + 7) / 8, NGUM = NA > 16 ? 5 : 4;
+    static_assert(NA <= 20, "noise passes");
+    auto draw_noise = [&](int q0, int q1) {
+#pragma nounroll
+      for (int q = q0; q < q1; ++q) {
+        const int a = q < 4 ? 4 * g + q : 16 + g;
+        L.nz[row * 32 + a] = gumbel24(L.draws[row * 24 + a] >> 8);
+      }
+    };
+    publish();
+    __builtin_amdgcn_s_setprio(3);
+    __syncthreads();  // the games are published
+    RL_STAMP_BEGIN
+    for (int k = 0; k < n_steps; ++k) {
+      const uint64_t t = t0 + (uint64_t)k;
+      __syncthreads();  // the movers' bit vectors
+      RL_STAMP(0)
+      if (lane < 16 * NBLK) {  // a Philox block per (game, 8 actions)
+        const Block4 b = draw_block(p.seed, (uint64_t)(p.env_base + e), t, (uint64_t)s.cur * 256u + (uint64_t)g, TAG_ACTION);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) L.draws[row * 24 + 8 * g + j] = block_u32(b, j);
+      }
+      wave_lds_sync();
+      draw_noise(0, 2);
+      RL_STAMP(10)
+      __syncthreads();  // h1
+      RL_STAMP(2)
+      draw_noise(2, NGUM);
+      // what the move needs beyond the action, and the last tile's weights of layer 3, ahead of the barrier
+      const uint32_t legal = hn_legal<G>(s);
+      const int next_card = hn_deck_card(s, s.next);
+      u32x4 w3[S2];
+#pragma unroll
+      for (int ks = 0; ks < S2; ++ks) w3[ks] = L.w3[((NT3 - 1) * S2 + ks) * 64 + lane];
+      RL_STAMP(3)
+      __syncthreads();  // h2; the decks
+      RL_STAMP(4)
+      // layer 3 transposed: lane 16 g + r holds row r, actions 16 j + 4 g .. + 3
+      const uint16_t* hr = L.h2 + row * LD + 8 * g;
+      f32x4 lg[NT3];
+#pragma unroll
+      for (int j = 0; j < NT3; ++j) lg[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < S2; ++ks) {
+        const u32x4 a = *reinterpret_cast<const u32x4*>(hr + ks * 32);
+#pragma unroll
+        for (int j = 0; j < NT3; ++j)
+          lg[j] = mfma_step(j == NT3 - 1 ? w3[ks] : L.w3[(j * S2 + ks) * 64 + lane], a, lg[j]);
+      }
+      float best_s = -INFINITY;
+      int best_a = 4 * g;
+#pragma unroll
+      for (int j = 0; j < NT3; ++j) {
+        const f32x4 nz4 = *reinterpret_cast<const f32x4*>(&L.nz[row * 32 + 16 * j + 4 * g]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int a = 16 * j + 4 * g + r;
+          const bool ok = a < NA && ((legal >> a) & 1u);
+          const float l = lg[j][r] + b3[j][r], sc = action_score(l, nz4[r], ok);
+          lg[j][r] = ok ? l : -INFINITY;
+          const bool take = sc > best_s;
+          best_s = take ? sc : best_s;
+          best_a = take ? a : best_a;
+        }
+      }
+#pragma unroll
+      for (int x = 16; x <= 32; x *= 2) {  // over the row's four lanes: the first index of the largest score
+        const float os = __shfl_xor(best_s, x);
+        const int oa = __shfl_xor(best_a, x);
+        const bool take = (os > best_s) | ((os == best_s) & (oa < best_a));
+        best_s = take ? os : best_s;
+        best_a = take ? oa : best_a;
+      }
+      RL_STAMP(5)
+      const int cur = s.cur;
+      float r;
+      uint32_t d;
+      hn_transition<G>(p, s, best_a, r, d, legal, [&]() { return next_card; });
+      if (d) hn_deal<G>(s, L.words[min(row, te_valid - 1)]);
+      publish();
+      RL_STAMP(8)
+      __syncthreads();  // the games are published
+      RL_STAMP(6)
+      if (out.logits && row < te_valid) {
+        float* lo = out.logits + ((size_t)k * E + e) * 2 * NA;
+#pragma unroll
+        for (int j = 0; j < NT3; ++j)
+          if (16 * j + 4 * g < NA) {
+            const f32x4 none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            // (4-byte aligned vectors)
+            __builtin_memcpy(__builtin_assume_aligned(lo + cur * NA + 16 * j + 4 * g, 4), &lg[j], 16);
+            __builtin_memcpy(__builtin_assume_aligned(lo + (1 - cur) * NA + 16 * j + 4 * g, 4), &none, 16);
+          }
+      }
+      if (owner) {
+        if (out.actions) {
+          out.actions[((size_t)k * E + e) * 2 + cur] = best_a;
+          out.actions[((size_t)k * E + e) * 2 + 1 - cur] = 0;
+        }
+        if (out.reward) out.reward[(size_t)k * E + e] = r;
+        if (out.done) out.done[(size_t)k * E + e] = (uint8_t)d;
+      }
+      RL_STAMP(7)
+    }
+    RL_STAMP_END(0)
+    if (out.obs_last) __syncthreads();  // both rows' bit vectors
+    if (owner) hn_store(state, E, e, s);
+    return;
+  }
+
+  // ------------------------------------------------------- helper waves ----
+  const int hw = wave - 9;
+  // The decks of games g0 .. g0 + DG - 1 flagged in may_end, drawn at step t, by one wave: the swap
+  // positions, a Philox block per lane, then the swaps of hn_wave_deck's shuffle in their own
+  // order on the deck's bytes in LDS, one lane per game (a chain of LDS latencies, but all games
+  // at once: hn_wave_deck would take a wave's 350 instructions per game).
+  constexpr int BW = G::NB <= 4 ? 4 : 8;      // lanes per game of the draws
+  constexpr int ND = TE * BW / 64, DG = TE / ND;  // deck waves, games of each: all of a wave's draws in one pass
+  auto draw_swaps = [&](uint64_t t, int g0) {
+    const int blk = lane & (BW - 1), el = g0 + lane / BW;
+    if (!__builtin_amdgcn_ballot_w64(L.may_end[el] != 0)) return;
+    if (blk < G::NB && L.may_end[el]) {
+      const Block4 b = draw_block(p.seed, (uint64_t)(p.env_base + e0 + el), t, (uint64_t)blk, TAG_RESET);
+      uint32_t w[2] = {0, 0};
+#pragma unroll
+      for (int q = 0; q < 8; ++q)  // draw k swaps position CARDS-1 - k with one of CARDS - k
+        w[q >> 2] |= range_map(block_u32(b, q), (uint32_t)max(G::CARDS - 8 * blk - q, 0)) << (8 * (q & 3));
+      L.swaps[el][2 * blk] = w[0];
+      L.swaps[el][2 * blk + 1] = w[1];
+    }
+    for (int i = lane; i < DG * HN_DECK_WORDS; i += 64) {
+      const int j = i / HN_DECK_WORDS;
+      L.words[g0 + j][i - j * HN_DECK_WORDS] = L.order[i - j * HN_DECK_WORDS];
+    }
+    wave_lds_sync();
+  };
+  // words of swap positions; those worked off under layer 1 (the small game's layers are short and its decks small)
+  constexpr int SW = (G::CARDS + 2) / 4, SW1 = ND > 1 ? SW / 2 : SW;
+  auto swap_cards = [&](int g0, int w0, int w1) {
+    if (lane < DG && L.may_end[g0 + lane]) {
+      uint8_t* d = reinterpret_cast<uint8_t*>(L.words[g0 + lane]);
+#pragma nounroll
+      for (int w = w0; w < w1; ++w) {
+        const uint32_t jw = L.swaps[g0 + lane][w];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = G::CARDS - 1 - 4 * w - q, j = (int)((jw >> (8 * q)) & 0xffu);
+          if (i > 0) {
+            const uint8_t x = d[i], y = d[j];
+            d[i] = y;
+            d[j] = x;
+          }
+        }
+      }
+    }
+  };
+  // nr rows of bits to consecutive global rows, by one wave: first without the gaps between rows
+  // (a 32-bit word from at most two rows), so that an output vector's 8 features are one byte
+  auto copy_rows = [&](int nr, const uint64_t* rows, uint16_t* dst) {
+    const uint32_t* w32 = reinterpret_cast<const uint32_t*>(rows);
+    uint32_t* flat = L.flat[hw];
+    for (int j = lane; j < (nr * G::OBS + 31) / 32; j += 64) {
+      const int r = 32 * j / G::OBS, c = 32 * j - r * G::OBS, sh = c & 31, left = G::OBS - c;
+      const uint32_t* w = w32 + r * 2 * HN_OBS_WORDS + (c >> 5);
+      uint32_t x = __builtin_amdgcn_alignbit(w[1], w[0], sh);  // (the bits past a row's end are 0)
+      if (left < 32 && r + 1 < nr) x |= w32[(r + 1) * 2 * HN_OBS_WORDS] << left;
+      flat[j] = x;
+    }
+    wave_lds_sync();
+    hn_write_flat<G, uint16_t, HN_FS_ROWS * G::OBS, 1, false>(reinterpret_cast<uint8_t*>(flat), nr * G::OBS, dst, 0, lane,
+                                                              L.lut);
+  };
+  __builtin_amdgcn_s_setprio(2);  // (the older MLP waves would go first at the memory pipe)
+  __syncthreads();  // the games are published
+  RL_STAMP_BEGIN
+  for (int k = 0; k < n_steps; ++k) {
+    __syncthreads();  // the movers' bit vectors
+    RL_STAMP(0)
+    if (hw < ND) {
+      draw_swaps(t0 + (uint64_t)k + 1, hw * DG);
+      swap_cards(hw * DG, 0, SW1);
+    } else {
+      build_rows(false, tid - 576 - 64 * ND, 192 - 64 * ND);
+    }
+    RL_STAMP(10)
+    __syncthreads();  // h1, the other rows' bit vectors
+    RL_STAMP(2)
+    if (hw < ND) swap_cards(hw * DG, SW1, SW);
+    RL_STAMP(9)
+    const int r0 = HN_FS_ROWS * hw, nr = min(HN_FS_ROWS, 2 * te_valid - r0);
+    if (nr > 0) {
+      if (out.obs) copy_rows(nr, L.bits[r0], static_cast<uint16_t*>(out.obs) + (((size_t)k * E + e0) * 2 + r0) * G::OBS);
+      wave_lds_sync();
+      for (int j = lane; j < nr * HN_OBS_WORDS; j += 64) L.bits[r0][j] = 0;
+    }
+    RL_STAMP(3)
+    __syncthreads();  // h2; o_t is copied out and its bit vectors are clear; the decks
+    RL_STAMP(4)
+    __syncthreads();  // the games are published
+    RL_STAMP(6)
+  }
+  RL_STAMP_END(2)
+  if (out.obs_last) {
+    build_rows(false, tid - 576, 192);
+    __syncthreads();  // both rows' bit vectors
+  }
+}
+
 // ---------------------------------------------------------- launchers ----
 
 constexpr int HN_ENV_TE = 8;  // envs per workgroup of the init and env-only kernels
@@ -693,9 +1176,26 @@ static hipError_t launch_hn_step_g(const HnParams& p, int32_t* state, uint64_t t
   return hipGetLastError();
 }
 
+template <class G, int H>
+static hipError_t launch_hn_run_fs(const HnParams& p, const PolicyArgs& pol, int32_t* state, uint64_t t0,
+                                   int n_steps, const TrajArgs& out, hipStream_t s) {
+  constexpr size_t lds = sizeof(HnFsLds<G, H>);
+  static_assert(lds <= MAX_LDS_BYTES, "one workgroup per CU");
+  const hipError_t e = hipFuncSetAttribute((const void*)hn_run_fs_kernel<G, H>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hn_run_fs_kernel<G, H><<<hn_tiles(p.E, HN_RUN_TE), HN_FS_NT, lds, s>>>(p, pol, state, t0, n_steps, out);
+  return hipGetLastError();
+}
+
 template <class G>
 static hipError_t launch_hn_run_g(const HnParams& p, const PolicyArgs& pol, int32_t* state, uint64_t t0,
                                   int n_steps, const TrajArgs& out, hipStream_t s) {
+  // 256- and 512-wide packed policies: role-split kernel, faster from 1 to 16384 games (0.98 against 1.53 ms at 4096);
+  // it holds weights in registers and LDS, so the widths are compile-time
+  if (pol.Wp[0] != nullptr && pol.H1 == pol.H2 && (pol.H1 == 256 || pol.H1 == 512))
+    return pol.H1 == 512 ? launch_hn_run_fs<G, 512>(p, pol, state, t0, n_steps, out, s)
+                         : launch_hn_run_fs<G, 256>(p, pol, state, t0, n_steps, out, s);
   const size_t lds = hn_run_lds_bytes(pol);
   const bool pk = pol.dt == DT_BF16 && pol.Wp[0] != nullptr;  // fragment-major weights
   const void* fn = pol.dt == DT_F32 ? (const void*)hn_run_kernel<G, DT_F32, false>

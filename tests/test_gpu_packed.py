@@ -160,6 +160,42 @@ def test_lbf12_role_split_rollout(E, keep):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("E", [1, 15, 17, 40])
+@pytest.mark.parametrize("colours,H", [(5, 512), (5, 256), (3, 512), (3, 256)])
+@pytest.mark.parametrize("keep", [("obs", "actions", "logits", "reward", "done", "obs_last"), ("reward",), ("obs_last",)])
+def test_hanabi_role_split_rollout(E, colours, H, keep):
+    """256- and 512-wide packed Hanabi policies run on a kernel of their own: ragged tiles of 16 games, games that
+    end in every way (lives, last turn, step limit) inside the launch, a launch split in two and outputs left out
+    give the unpacked (general) kernel's results, bit for bit."""
+    require_gpu()
+    _note(f"Hanabi role-split rollout E={E} colours={colours} H={H} keep={keep}")
+    for max_steps in (11, 200):
+        cfg = R.hanabi_config(E, colours=colours, ranks=colours, env_base=77, seed=5, max_steps=max_steps)
+        D, nA = R.rl_obs_dim(cfg), R.rl_num_actions(cfg)
+        ws, bs = workloads.policy_weights((D, H, H, nA), seed=31, bias_scale=0.3)
+        bs[2][:5] += 2.0  # discard often: games of 200 steps reach the end of the deck
+        res = []
+        for pack in (True, False):
+            pol = R.Policy(ws, bs, "bf16", pack=pack)
+            state = R.new_state(cfg)
+            R.rollout_init(cfg, state)
+            got = []
+            for t0, T in ((0, 67), (67, 1), (68, 10)):
+                # (logits at a 4-byte aligned address)
+                out = dict(obs=torch.empty(T, E, 2, D, dtype=torch.bfloat16, device="cuda"),
+                           actions=torch.empty(T, E, 2, dtype=torch.int32, device="cuda"),
+                           logits=torch.empty(T * E * 2 * nA + 1, device="cuda")[1:].view(T, E, 2, nA),
+                           reward=torch.empty(T, E, device="cuda"),
+                           done=torch.empty(T, E, dtype=torch.uint8, device="cuda"),
+                           obs_last=torch.empty(E, 2, D, dtype=torch.bfloat16, device="cuda"))
+                out = {k: v for k, v in out.items() if k in keep}
+                R.rollout_run(cfg, pol, state, t0, T, **out)
+                got += [out[k].cpu() for k in keep] + [state.cpu().clone()]
+            res.append(got)
+        for a, b in zip(*res):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dims", [(432, 256, 256, 6), (658, 512, 512, 20), (1170, 256, 256, 6), (300, 512, 32, 20)])
 def test_packed_policy_forward_equals_unpacked(dims):
     """The tiled policy forward stages its weight slices from the packed copy: same logits, bit for bit."""
