@@ -206,13 +206,15 @@ def _need(t, name, dtype=None, shape=None):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
-def _need_state(cfg, state):
-    """The env state buffer: a contiguous int32 device tensor of exactly rl_state_bytes(cfg) bytes."""
+def _need_state(cfg, state, cc=None):
+    """The env state buffer: a contiguous int32 device tensor of exactly rl_state_bytes(cfg) bytes
+    (cc: the C struct of cfg, where the caller has it)."""
     if state is None:
         raise ValueError("state is required")
-    n = rl_state_bytes(cfg)
+    cc = ctypes.byref(cfg.c()) if cc is None else cc
+    n = lib.rl_state_bytes(cc)
     if n == 0:
-        _check(lib.rl_obs_dim(ctypes.byref(cfg.c())))
+        _check(lib.rl_obs_dim(cc))
     if state.numel() * state.element_size() != n:
         raise ValueError(f"state holds {state.numel() * state.element_size()} bytes; "
                          f"this config needs rl_state_bytes = {n}")
@@ -329,19 +331,21 @@ def new_state(cfg, device="cuda"):
 
 def rollout_init(cfg, state, obs=None, legal=None, stream=None):
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
-    _need_state(cfg, state)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
+    _need_state(cfg, state, cc)
     if obs is not None:
         _need(obs, "obs", shape=(E, A, D))
     _need(legal, "legal", torch.uint8, (E, A, nA))
     code = _DT_CODE.get(obs.dtype, -1) if obs is not None else RL_F32
-    _check(lib.rollout_init(ctypes.byref(cfg.c()), _ptr(state), _ptr(obs), code, _ptr(legal), _stream(stream)))
+    _check(lib.rollout_init(cc, _ptr(state), _ptr(obs), code, _ptr(legal), _stream(stream)))
 
 
 def rollout_step(cfg, state, t0, actions, obs_out=None, reward=None, done=None, legal_out=None, stream=None):
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
-    _need_state(cfg, state)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
+    _need_state(cfg, state, cc)
     _need(actions, "actions", torch.int32)
     if actions.dim() != 3 or tuple(actions.shape[1:]) != (E, A):
         raise ValueError(f"actions must be [T, {E}, {A}], got {tuple(actions.shape)}")
@@ -352,7 +356,7 @@ def rollout_step(cfg, state, t0, actions, obs_out=None, reward=None, done=None, 
     _need(done, "done", torch.uint8, (T, E))
     _need(legal_out, "legal_out", torch.uint8, (T, E, A, nA))
     code = _DT_CODE.get(obs_out.dtype, -1) if obs_out is not None else RL_F32
-    _check(lib.rollout_step(ctypes.byref(cfg.c()), _ptr(state), t0, T, _ptr(actions), _ptr(obs_out), code,
+    _check(lib.rollout_step(cc, _ptr(state), t0, T, _ptr(actions), _ptr(obs_out), code,
                             _ptr(reward), _ptr(done), _ptr(legal_out), _stream(stream)))
 
 
@@ -372,9 +376,10 @@ def policy_forward(policy, obs, legal=None, logits=None, stream=None):
 def rollout_run(cfg, policy, state, t0, n_steps, obs=None, actions=None, logits=None, reward=None, done=None,
                 obs_last=None, stream=None):
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(obs, "obs", policy.torch_dtype, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
     _need(logits, "logits", torch.float32, (T, E, A, nA))
@@ -384,7 +389,7 @@ def rollout_run(cfg, policy, state, t0, n_steps, obs=None, actions=None, logits=
     tr = _Traj(obs=_ptr(obs), actions=_ptr(actions), logits=_ptr(logits), reward=_ptr(reward), done=_ptr(done),
                obs_last=_ptr(obs_last))
     pc = policy.c()
-    _check(lib.rollout_run(ctypes.byref(cfg.c()), ctypes.byref(pc), _ptr(state), t0, T, ctypes.byref(tr),
+    _check(lib.rollout_run(cc, ctypes.byref(pc), _ptr(state), t0, T, ctypes.byref(tr),
                            _stream(stream)))
 
 
@@ -393,9 +398,10 @@ def rollout_run_ac(cfg, policy, state, t0, n_steps, value=None, logp=None, value
     """rollout_run for an actor-critic network (last layer: nA logits, then the value); also writes
     value [T, E, A], logp [T, E, A] and value_last [E, A]."""
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(obs, "obs", policy.torch_dtype, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
     _need(logits, "logits", torch.float32, (T, E, A, nA))
@@ -409,7 +415,7 @@ def rollout_run_ac(cfg, policy, state, t0, n_steps, value=None, logp=None, value
                obs_last=_ptr(obs_last))
     ac = _AcTraj(value=_ptr(value), logp=_ptr(logp), value_last=_ptr(value_last))
     pc = policy.c()
-    _check(lib.rollout_run_ac(ctypes.byref(cfg.c()), ctypes.byref(pc), _ptr(state), t0, T, ctypes.byref(tr),
+    _check(lib.rollout_run_ac(cc, ctypes.byref(pc), _ptr(state), t0, T, ctypes.byref(tr),
                               ctypes.byref(ac), _stream(stream)))
 
 
@@ -418,10 +424,11 @@ def rollout_run_teams(cfg, policy, teammates, state, t0, n_steps, obs=None, acti
     """rollout_run where agent a of env e acts with heuristic teammates[e, a] (0..8, see HEURISTICS) or,
     for any other value, with the policy."""
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
     _need(teammates, "teammates", torch.int32, (E, A))
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(obs, "obs", policy.torch_dtype, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
     _need(logits, "logits", torch.float32, (T, E, A, nA))
@@ -431,7 +438,7 @@ def rollout_run_teams(cfg, policy, teammates, state, t0, n_steps, obs=None, acti
     tr = _Traj(obs=_ptr(obs), actions=_ptr(actions), logits=_ptr(logits), reward=_ptr(reward), done=_ptr(done),
                obs_last=_ptr(obs_last))
     pc = policy.c()
-    _check(lib.rollout_run_teams(ctypes.byref(cfg.c()), ctypes.byref(pc), _ptr(teammates), _ptr(state), t0, T,
+    _check(lib.rollout_run_teams(cc, ctypes.byref(pc), _ptr(teammates), _ptr(state), t0, T,
                                  ctypes.byref(tr), _stream(stream)))
 
 
@@ -495,9 +502,10 @@ def rollout_run_s5(cfg, policy, state, carry, t0, n_steps, value=None, logp=None
     """rollout_run_ac with the recurrent S5 actor-critic; ``carry`` [E * A, 2, P] float32 is the S5 state.
     ``workspace``: a uint8 device tensor of at least s5_workspace_bytes(cfg, policy) bytes (allocated when None)."""
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(carry, "carry", torch.float32, (E * A, 2, policy.P))
     _need(obs, "obs", torch.bfloat16, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
@@ -509,13 +517,13 @@ def rollout_run_s5(cfg, policy, state, carry, t0, n_steps, value=None, logp=None
     _need(logp, "logp", torch.float32, (T, E, A))
     _need(value_last, "value_last", torch.float32, (E, A))
     pc = policy.c()
-    nbytes = lib.rl_s5_workspace_bytes(ctypes.byref(cfg.c()), ctypes.byref(pc))
+    nbytes = lib.rl_s5_workspace_bytes(cc, ctypes.byref(pc))
     if workspace is None:
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=carry.device)
     tr = _Traj(obs=_ptr(obs), actions=_ptr(actions), logits=_ptr(logits), reward=_ptr(reward), done=_ptr(done),
                obs_last=_ptr(obs_last))
     ac = _AcTraj(value=_ptr(value), logp=_ptr(logp), value_last=_ptr(value_last))
-    _check(lib.rollout_run_s5(ctypes.byref(cfg.c()), ctypes.byref(pc), _ptr(state), _ptr(carry), t0, T,
+    _check(lib.rollout_run_s5(cc, ctypes.byref(pc), _ptr(state), _ptr(carry), t0, T,
                               ctypes.byref(tr), ctypes.byref(ac), _ptr(workspace), workspace.numel(),
                               _stream(stream)))
     return workspace
@@ -525,9 +533,10 @@ def rollout_run_s5_noalloc(cfg, policy, state, carry, t0, n_steps, value=None, l
                            actions=None, logits=None, reward=None, done=None, obs_last=None, stream=None):
     """rollout_run_s5 on the library's built-in device scratch (no workspace, nothing allocated)."""
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(carry, "carry", torch.float32, (E * A, 2, policy.P))
     _need(obs, "obs", torch.bfloat16, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
@@ -541,7 +550,7 @@ def rollout_run_s5_noalloc(cfg, policy, state, carry, t0, n_steps, value=None, l
     tr = _Traj(obs=_ptr(obs), actions=_ptr(actions), logits=_ptr(logits), reward=_ptr(reward), done=_ptr(done),
                obs_last=_ptr(obs_last))
     ac = _AcTraj(value=_ptr(value), logp=_ptr(logp), value_last=_ptr(value_last))
-    _check(lib.rollout_run_s5_noalloc(ctypes.byref(cfg.c()), ctypes.byref(policy.c()), _ptr(state), _ptr(carry), t0,
+    _check(lib.rollout_run_s5_noalloc(cc, ctypes.byref(policy.c()), _ptr(state), _ptr(carry), t0,
                                       T, ctypes.byref(tr), ctypes.byref(ac), _stream(stream)))
 
 
@@ -565,10 +574,11 @@ def rollout_run_pop(cfg, pop, policy_index, state, t0, n_steps, obs=None, action
                     done=None, obs_last=None, stream=None):
     """rollout_run with agent a of env e acting with policy policy_index[e, a] of the population ``pop``."""
     E, A = cfg.n_envs, cfg.n_agents
-    D, nA = rl_obs_dim(cfg), rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())  # (2 us: built once per call)
+    D, nA = lib.rl_obs_dim(cc), lib.rl_num_actions(cc)
     T = n_steps
     _need(policy_index, "policy_index", torch.int32, (E, A))
-    _need_state(cfg, state)
+    _need_state(cfg, state, cc)
     _need(obs, "obs", pop.torch_dtype, (T, E, A, D))
     _need(actions, "actions", torch.int32, (T, E, A))
     _need(logits, "logits", torch.float32, (T, E, A, nA))
@@ -578,18 +588,19 @@ def rollout_run_pop(cfg, pop, policy_index, state, t0, n_steps, obs=None, action
     tr = _Traj(obs=_ptr(obs), actions=_ptr(actions), logits=_ptr(logits), reward=_ptr(reward), done=_ptr(done),
                obs_last=_ptr(obs_last))
     pc = pop.c()
-    _check(lib.rollout_run_pop(ctypes.byref(cfg.c()), ctypes.byref(pc), pop.n, _ptr(policy_index), _ptr(state), t0,
+    _check(lib.rollout_run_pop(cc, ctypes.byref(pc), pop.n, _ptr(policy_index), _ptr(state), t0,
                                T, ctypes.byref(tr), _stream(stream)))
 
 
 def rollout_sample(cfg, t, logits, legal=None, actions=None, stream=None):
-    E, A, nA = cfg.n_envs, cfg.n_agents, rl_num_actions(cfg)
+    cc = ctypes.byref(cfg.c())
+    E, A, nA = cfg.n_envs, cfg.n_agents, lib.rl_num_actions(cc)
     _need(logits, "logits", torch.float32, (E, A, nA))
     _need(legal, "legal", torch.uint8, (E, A, nA))
     if actions is None:
         actions = torch.empty(E, A, dtype=torch.int32, device=logits.device)
     _need(actions, "actions", torch.int32, (E, A))
-    _check(lib.rollout_sample(ctypes.byref(cfg.c()), t, _ptr(logits), _ptr(legal), _ptr(actions), _stream(stream)))
+    _check(lib.rollout_sample(cc, t, _ptr(logits), _ptr(legal), _ptr(actions), _stream(stream)))
     return actions
 
 
