@@ -389,7 +389,8 @@ def kernel_role(name):
         return "env"
     if "gae" in name:
         return "gae"
-    if any(k in name for k in ("lbf_rollout_kernel", "_run_kernel", "_run_pop_kernel", "_pop2_kernel", "s5_")):
+    if any(k in name for k in ("lbf_rollout_kernel", "_run_kernel", "_run_fs_kernel", "_run_pop_kernel", "_pop2_kernel",
+                               "s5_")):
         return "run"
     if "copyBuffer" in name:
         return "copy"
