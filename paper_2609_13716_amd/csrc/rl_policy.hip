@@ -430,9 +430,15 @@ static bool try_launch_policy_reg(const PolicyArgs& pol, const void* obs, const 
 // 1.9 GHz, and a layer's tanh epilogue (128 values per lane at about 34 cycles) is
 // hidden only as far as the two workgroups of a CU drift apart.  Tiles of 64 rows
 // with the weights staged through LDS moved 60 KB of LDS per 64-row K step
-// (480 cycles against 256 of MFMA): 1170-256-256-6 over 262144 rows 360 -> 224 us,
-// 658-512-512-20 over 100003 rows 328 -> 159 us, 432-256-256-6 over 262144 rows
-// 181 -> 102 us.  Loading the rows two stages ahead, or as single words, changed nothing.
+// (480 cycles against 256 of MFMA): 1170-256-256-6 over 262144 rows 360 -> 223 us,
+// 658-512-512-20 over 100003 rows with legality masks 328 -> 166 us, 432-256-256-6
+// over 262144 rows 159 -> 102 us.  Loading the rows two stages ahead, or as single
+// words, changed nothing.
+// HBM reads over 262144 rows: at a row pitch that is no multiple of 128 bytes a stage
+// ends inside a line, and 5-17% of the lines are read twice (1170-256-256-6 708 MB for
+// 613 MB of rows; 1152 features, whole lines, 635 for 604); and each XCD reads the
+// weights anew for about every round of workgroups (640-512-512-20, whole lines: 413 MB
+// for 335 MB of rows, 66 times its 1.2 MB of weights).
 constexpr int PT_SK = 64;  // features per staged slice: two MFMA K steps
 
 template <int H, int MT>
@@ -485,7 +491,11 @@ __global__ __launch_bounds__(H, H == 256 ? 2 : 1) void policy_fwd_tiled_kernel(P
     bias_s[i] = bf16_to_f32(i < H ? static_cast<const uint16_t*>(pol.b[0])[i]
                                   : static_cast<const uint16_t*>(pol.b[1])[i - H]);
 
-  // weight operands of a layer: unit tile 4 wave + u, K step st
+  // Weight operands of a layer: unit tile 4 wave + u, K step st.  An unpacked tile is
+  // loaded with four consecutive lanes on the 64 bytes of a row and moved to the
+  // operand's lanes when it is used (a lane per row and 16 bytes, as the MFMA takes it,
+  // touches 16 lines every 16 lanes, about 20 bytes per clock: 64-256-256-6 at 32768
+  // rows 16.2 against 13.4 us, 2048-512-512-6 at 1024 rows 76.5 against 38.6).
   auto w_rsrc = [&](int l, int K) {
     const int S = (K + 31) / 32;
     return PK ? pt_rsrc(pol.Wp[l], (uint32_t)(H / 16) * S * 1024) : pt_rsrc(pol.W[l], (uint32_t)H * K * 2);
@@ -494,7 +504,15 @@ __global__ __launch_bounds__(H, H == 256 ? 2 : 1) void policy_fwd_tiled_kernel(P
     const int S = (K + 31) / 32;
 #pragma unroll
     for (int u = 0; u < UT; ++u)
-      wo[u] = PK ? ((4 * wave + u) * S * 64 + lane) * 16 : ((64 * wave + 16 * u + (lane & 15)) * K + 8 * (lane >> 4)) * 2;
+      wo[u] = PK ? ((4 * wave + u) * S * 64 + lane) * 16 : ((64 * wave + 16 * u + (lane >> 2)) * K + 8 * (lane & 3)) * 2;
+  };
+  auto w_operand = [&](u32x4 v) -> u32x4 {
+    if constexpr (PK) return v;
+    u32x4 o;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+      o[d] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (4 * (lane & 15) + (lane >> 4)), (int)v[d]);
+    return o;
   };
   auto w_load = [&](__amdgpu_buffer_rsrc_t r, int off, int st) -> u32x4 {
     return __builtin_amdgcn_raw_buffer_load_b128(r, off, st * (PK ? 1024 : 64), 0);
@@ -564,15 +582,13 @@ __global__ __launch_bounds__(H, H == 256 ? 2 : 1) void policy_fwd_tiled_kernel(P
         const int left = D - st * 32 - 8 * (lane >> 4);
 #pragma unroll
         for (int m = 0; m < MT; ++m) b[m] = pt_mask8(b[m], left);
-        if constexpr (!PK) {
-#pragma unroll
-          for (int u = 0; u < UT; ++u) wr[KK][u] = pt_mask8(wr[KK][u], left);
-        }
       }
 #pragma unroll
       for (int u = 0; u < UT; ++u) {
+        u32x4 a = w_operand(wr[KK][u]);
+        if (!PK && st * 32 + 32 > D) a = pt_mask8(a, D - st * 32 - 8 * (lane >> 4));
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(wr[KK][u], b[m], acc[u][m]);
+        for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(a, b[m], acc[u][m]);
         wr[KK][u] = w_load(wres, wo[u], st + 2);  // (past the last step: unused)
       }
     };
@@ -615,8 +631,9 @@ __global__ __launch_bounds__(H, H == 256 ? 2 : 1) void policy_fwd_tiled_kernel(P
         for (int m = 0; m < MT; ++m) b[m] = *reinterpret_cast<const u32x4*>(hb + m * 16 * L::LDH + (st + kk) * 32);
 #pragma unroll
         for (int u = 0; u < UT; ++u) {
+          const u32x4 a = w_operand(wr[kk][u]);
 #pragma unroll
-          for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(wr[kk][u], b[m], acc[u][m]);
+          for (int m = 0; m < MT; ++m) acc[u][m] = mfma16<DT_BF16>(a, b[m], acc[u][m]);
           wr[kk][u] = w_load(wres, wo[u], st + kk + 2);
         }
       }
@@ -679,17 +696,34 @@ static hipError_t launch_policy_tiled_mt(const PolicyArgs& pol, const void* obs,
 // workgroups, and a workgroup of MT row tiles costs about k + MT: the weights
 // it reads and its prologue are the constant part (k = 3 at 256 units, two workgroups
 // sharing the CU; 2 at 512).  The least product is taken, the larger tile on
-// ties.  Measured over MT 1, 2, 4, 5, 6, 7, 8 (us; chosen one starred):
+// ties.  Packed weights, measured over MT 1, 2, 4, 5, 6, 7, 8 (us; chosen one starred):
 // 1170-256-256-6 at 262144 rows 648, 415, 269, 264, 250, 243, 224*; at 16384
 // rows 35, 22.7, 23.3*, 26, 27, 31, 33; at 4096 rows 13.0*, 13.0, 17, 21, 23, 27, 28;
 // 658-512-512-20 at 100003 rows 317, 189, 169, 159*, 175, 156, 173; at 98304
 // rows 345, 188, 154, 159, 145, 156, 135*.
-static int pt_pick_mt(int H, int64_t rows) {
+//
+// The product counts two workgroups on a CU as twice the time of one.  At 256 units
+// with packed weights two of MT 4 take 1.2 to 1.4 times the time of one, so that MT 4
+// is the best tile as long as all its workgroups are resident and fewer, larger
+// tiles would leave a CU one workgroup: 20481 to 32768 rows (32768 rows of 34, 432
+// and 1170 features, MT 4 against the 8 of the product: 11.4 and 14.6, 16.3 and 20.2,
+// 28.8 and 33.3 us; 22000 rows, against 6: 11.0 and 12.1, 14.7 and 15.8, 27.2 and
+// 27.2; up to 20480 rows MT 5 is as good or up to 5% better).  With unpacked weights
+// that holds for narrow rows only (32768 rows of 64, 192, 432, 658 features: 13.3 and
+// 15.8, 15.8 and 17.8, 23.9 and 24.1, 32.9 and 30.2; 24576 rows, against 6: 13.3 and
+// 13.4, 15.6 and 15.2, 21.2 and 19.6).  Unpacked forwards over 1 to 131072 rows of 16
+// to 2048 features then take 0.34 to 1.05 of their time in 64-row tiles with the weights
+// staged through LDS (192-256-256-6 at 30000 rows 16.2 staged, 15.7 here;
+// 658-512-512-6 at 100003 rows 335 and 200 us); the 1.05 is 0.6 us at 16 features
+// and 20481 rows.
+constexpr int PT_CUS = 256;
+static int pt_pick_mt(int H, int D, bool packed, int64_t rows) {
+  if (H == 256 && (packed || D <= 192) && rows > 16 * 5 * PT_CUS && rows <= 16 * 4 * 2 * PT_CUS) return 4;
   const int k = H == 256 ? 3 : 2;
   int best = 8;
   int64_t best_cost = INT64_MAX;
   for (int mt : {8, 7, 6, 5, 4, 2, 1}) {
-    const int64_t wgs = (rows + 16 * mt - 1) / (16 * mt), cost = (wgs + 255) / 256 * (k + mt);
+    const int64_t wgs = (rows + 16 * mt - 1) / (16 * mt), cost = (wgs + PT_CUS - 1) / PT_CUS * (k + mt);
     if (cost < best_cost) {
       best_cost = cost;
       best = mt;
@@ -701,7 +735,7 @@ static int pt_pick_mt(int H, int64_t rows) {
 template <int H, bool PK>
 static hipError_t launch_policy_tiled(const PolicyArgs& pol, const void* obs, const uint8_t* legal, int64_t rows,
                                       float* logits, hipStream_t s) {
-  switch (pt_pick_mt(H, rows)) {
+  switch (pt_pick_mt(H, pol.D, PK, rows)) {
     case 1: return launch_policy_tiled_mt<H, 1, PK>(pol, obs, legal, rows, logits, s);
     case 2: return launch_policy_tiled_mt<H, 2, PK>(pol, obs, legal, rows, logits, s);
     case 4: return launch_policy_tiled_mt<H, 4, PK>(pol, obs, legal, rows, logits, s);

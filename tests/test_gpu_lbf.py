@@ -518,7 +518,7 @@ def test_policy_forward_tile_sizes(dims, pack):
         if l < 2:
             x = torch.tanh(x).to(torch.bfloat16).float()
     assert_logits_close(full.cpu().numpy(), x.cpu().numpy(), RTOL["bf16"])
-    for rows in (1, 17, 4097, 8193, 16385, 20481, 24577, 28673, 32769, 50001):
+    for rows in (1, 17, 4097, 8193, 16385, 20481, 24577, 28673, 32768, 32769, 40961, 49153, 50001, 57345):
         part = buf[:rows].clone()
         assert torch.equal(R.policy_forward(pol, part), full[:rows]), rows
     nan = buf[:40].clone()
