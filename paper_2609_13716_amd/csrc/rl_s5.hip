@@ -559,6 +559,9 @@ __global__ __launch_bounds__(S5_NT) void s5_out_kernel(S5OutArgs o) {
 // 30.1 us staged (which also multiplied every C x tile twice when H <= 128), 19.0 us here.
 constexpr int FR_P = 3;  // weight blocks in flight
 
+// Four floats of the caller's carried state, which need only be float-aligned.
+typedef f32x4 carry4 __attribute__((aligned(4)));
+
 // Fragment-major copy of a float32 W [N x K], N and K multiples of 16.
 __global__ void s5_packf_kernel(int N, int K, const float* __restrict__ W, float* __restrict__ out) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;  // 16-byte lane block
@@ -646,7 +649,7 @@ __global__ __launch_bounds__(S5F_NT) void s5_front_frag_kernel(S5FrontArgs a, co
     const bool keep = a.state[(size_t)a.step_plane * a.E + row / a.A] != 0;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(a.carry + (size_t)row * 2 * P + c * P + p0);
+      const f32x4 v = *reinterpret_cast<const carry4*>(a.carry + (size_t)row * 2 * P + c * P + p0);
 #pragma unroll
       for (int q = 0; q < 4; ++q) xo[m][c][q] = keep ? v[q] : 0.f;
     }
@@ -701,8 +704,8 @@ __global__ __launch_bounds__(S5F_NT) void s5_front_frag_kernel(S5FrontArgs a, co
       *reinterpret_cast<f32x4*>(xf + rl * L.ldxf + p0) = nr;
       *reinterpret_cast<f32x4*>(xf + rl * L.ldxf + P + p0) = ni;
       if (a.commit && row < a.R) {
-        *reinterpret_cast<f32x4*>(a.carry + (size_t)row * 2 * P + p0) = nr;
-        *reinterpret_cast<f32x4*>(a.carry + (size_t)row * 2 * P + P + p0) = ni;
+        *reinterpret_cast<carry4*>(a.carry + (size_t)row * 2 * P + p0) = nr;
+        *reinterpret_cast<carry4*>(a.carry + (size_t)row * 2 * P + P + p0) = ni;
       }
     }
   }

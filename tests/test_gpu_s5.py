@@ -200,3 +200,42 @@ def test_fused_heads_equal_gemm_heads(H, P, E):
         res.append([v[:, -small:].cpu() for v in out.values()] + [last[-small:].cpu(), carry[-2 * small:].cpu()])
     for a, b in zip(*res):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("grid", [8, 7])
+@pytest.mark.parametrize("full", [True, False])
+def test_fused_heads_partial_outputs_split_calls_and_carry_alignment(grid, full):
+    """The route of large batches with observations of whole and of broken 16-byte vectors (8x8: 192 features, 7x7:
+    147), with all outputs and with rewards only (observations in the workspace), in one call and in two (the
+    weight copies made anew, the state and the carry handed over), the carry at an address that is only 4-byte
+    aligned: the trajectories of a small batch's route in one call, bit for bit."""
+    require_gpu()
+    _note(f"S5 fused route grid={grid} full={full}")
+    E, small, T, H, P = 2079, 77, 5, 64, 32
+    D = 3 * grid * grid
+    pol = R.S5Policy(workloads.s5_params(D, H, P, 1024, 6, seed=9))
+    res = []
+    for n, calls, pad in ((small, ((0, T),), 0), (E, ((0, T),), 1), (E, ((0, 3), (3, T - 3)), 1)):
+        cfg = R.EnvConfig(n_envs=n, grid_h=grid, grid_w=grid, seed=3, max_steps=3, env_base=0 if n == E else E - small)
+        state = R.new_state(cfg)
+        R.rollout_init(cfg, state)
+        carry = torch.zeros(n * 2 * 2 * P + pad, device="cuda")[pad:].view(n * 2, 2, P)
+        got = []
+        for t0, steps in calls:
+            out = dict(reward=torch.empty(steps, n, device="cuda"))
+            if full:
+                out.update(obs=torch.empty(steps, n, 2, D, dtype=torch.bfloat16, device="cuda"),
+                           actions=torch.empty(steps, n, 2, dtype=torch.int32, device="cuda"),
+                           logits=torch.empty(steps, n, 2, 6, device="cuda"),
+                           done=torch.empty(steps, n, dtype=torch.uint8, device="cuda"),
+                           value=torch.empty(steps, n, 2, device="cuda"), logp=torch.empty(steps, n, 2, device="cuda"))
+            last = dict(value_last=torch.empty(n, 2, device="cuda"),
+                        obs_last=torch.empty(n, 2, D, dtype=torch.bfloat16, device="cuda")) if full else {}
+            R.rollout_run_s5(cfg, pol, state, carry, t0, steps, **out, **last)
+            torch.cuda.synchronize()
+            got.append(out)
+        res.append([torch.cat([g[k] for g in got])[:, -small:] for k in got[0]] + [v[-small:] for v in last.values()] +
+                   [carry[-2 * small:], state.view(-1, n)[:, -small:]])
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert torch.equal(a, b)
