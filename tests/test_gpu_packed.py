@@ -196,9 +196,42 @@ def test_hanabi_role_split_rollout(E, colours, H, keep):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("env", ["oc", "lbf12", "hn", "hn_mini"])
+def test_role_split_rollouts_of_many_workgroups(env):
+    """The role-split kernels over 257 workgroups (more than one round of the compute units), the last one ragged,
+    with the kitchens' and games' observations at addresses that are only 4-byte aligned, as the general kernels'
+    results, bit for bit."""
+    require_gpu()
+    E, T = 4099, 12
+    _note(f"role-split rollout {env} E={E}")
+    cfg = {"oc": lambda: R.overcooked_config(E, cook_time=2, max_steps=9, seed=5),
+           "lbf12": lambda: R.EnvConfig(n_envs=E, seed=6, **dict(workloads.WORKLOADS["lbf12_16k"]["env"], max_steps=9,
+                                                                 max_food_level=1)),
+           "hn": lambda: R.hanabi_config(E, seed=5, max_steps=9),
+           "hn_mini": lambda: R.hanabi_config(E, seed=5, max_steps=9, colours=3, ranks=3)}[env]()
+    A, D, nA, H = cfg.n_agents, R.rl_obs_dim(cfg), R.rl_num_actions(cfg), 512 if env == "hn" else 256
+    pad = 0 if env == "lbf12" else 2  # elements before the observations
+    ws, bs = workloads.policy_weights((D, H, H, nA), seed=37, bias_scale=0.3)
+    res = []
+    for pack in (True, False):
+        pol = R.Policy(ws, bs, "bf16", pack=pack)
+        state = R.new_state(cfg)
+        R.rollout_init(cfg, state)
+        shapes = dict(obs=(T, E, A, D), obs_last=(E, A, D))
+        out = {k: torch.empty(int(np.prod(v)) + pad, dtype=torch.bfloat16, device="cuda")[pad:].view(v)
+               for k, v in shapes.items()}
+        out.update(actions=torch.empty(T, E, A, dtype=torch.int32, device="cuda"),
+                   logits=torch.empty(T, E, A, nA, device="cuda"), reward=torch.empty(T, E, device="cuda"),
+                   done=torch.empty(T, E, dtype=torch.uint8, device="cuda"))
+        R.rollout_run(cfg, pol, state, 0, T, **out)
+        res.append(dict(out, state=state))
+    for k in res[0]:
+        assert torch.equal(res[0][k], res[1][k]), k
+
+
 @pytest.mark.parametrize("dims", [(432, 256, 256, 6), (658, 512, 512, 20), (1170, 256, 256, 6), (300, 512, 32, 20)])
 def test_packed_policy_forward_equals_unpacked(dims):
-    """The tiled policy forward stages its weight slices from the packed copy: same logits, bit for bit."""
+    """The tiled policy forward reads its MFMA operands from the packed copy: same logits, bit for bit."""
     require_gpu()
     _note(f"packed vs unpacked policy_forward {dims}")
     rng = np.random.default_rng(dims[0])
