@@ -118,10 +118,11 @@ typedef struct {
   const void* b[3];
   /* Optional (RL_BF16 only): a copy of W[0..2] in the fragment-major layout
    * written by rl_policy_pack, or NULL.  When set, the streamed-weight
-   * kernels (the kitchen and Hanabi rollouts, the wide-layer policy_forward)
-   * read their operands from it, 1 KB contiguous per load instead of 16 rows
-   * x 64 bytes; results are bit-identical to reading W.  Must be 16-byte aligned and stay valid and
-   * unchanged while calls that use the policy run. */
+   * kernels (the kitchen, Hanabi, 12x12 LBF and population rollouts, the
+   * wide-layer policy_forward) read their operands from it, 1 KB contiguous
+   * per load instead of 16 rows x 64 bytes; results are bit-identical to
+   * reading W.  Must be 16-byte aligned and stay valid and unchanged while
+   * calls that use the policy run. */
   const void* packed;
 } rl_policy;
 
@@ -295,7 +296,7 @@ rl_status rollout_run_teams(const rl_env_config* cfg, const rl_policy* policy, c
  * al., NeurIPS 2023.  Dense layers are bfloat16 (nn.Linear layout [out, in]),
  * every product accumulates in float32 and u, y and the head activations are
  * rounded to bfloat16; the S5 parameters and state are float32.  Every
- * pointer is device memory, 16-byte aligned.
+ * pointer of the struct is device memory, 16-byte aligned.
  * Limits: dtype RL_BF16; H a multiple of 64 in 64..256; P a multiple of 16 in
  * 16..128; F a multiple of 128 in 128..4096; nA in 1..16; D (the env's
  * observation size) at most 1024, and the encoder/S5 tile within 160 KiB of
@@ -328,8 +329,9 @@ rl_status rl_s5_discretize(int32_t d_state, int32_t d_model, const float* lambda
                            const float* b, float* lambda_bar, float* b_bar, void* stream);
 
 /* Bytes of the device workspace rollout_run_s5 needs for cfg and policy
- * (hidden activations of both heads, y, two observation tiles, actions);
- * 0 if either is invalid. */
+ * (hidden activations of both heads, or for large batches the weight copies
+ * that a call makes in their place; y, two observation tiles, actions, the
+ * concatenated C); 0 if either is invalid. */
 size_t rl_s5_workspace_bytes(const rl_env_config* cfg, const rl_s5_policy* policy);
 
 /* The rollout loop of rollout_run_ac with the recurrent S5 actor-critic
@@ -339,13 +341,16 @@ size_t rl_s5_workspace_bytes(const rl_env_config* cfg, const rl_s5_policy* polic
  *   carry      [E * A, 2, P] float32 (rows env-major; real then imaginary
  *              parts): the S5 state of every agent, read and left at step
  *              t0 + n_steps; its content is irrelevant for rows that start an
- *              episode at t0 (zeros are a valid start).
+ *              episode at t0 (zeros are a valid start).  Float alignment
+ *              suffices.
  *   out, ac    as rollout_run_ac; value_last is V(o_{t0+T}) computed without
  *              advancing carry.
  *   workspace  rl_s5_workspace_bytes(cfg, policy) bytes of device memory,
  *              owned by the caller, not read across calls.
  * The call is a sequence of kernels on `stream` (per step: encoder and S5,
- * three head layers, output layers and sampling, env step). */
+ * three head layers, output layers and sampling, env step; large batches with
+ * F = 1024: first the weight copies into the workspace, then per step encoder
+ * and S5, whole heads with their outputs, env step). */
 rl_status rollout_run_s5(const rl_env_config* cfg, const rl_s5_policy* policy, void* state, float* carry,
                          uint64_t t0, int32_t n_steps, const rl_traj* out, const rl_ac_traj* ac, void* workspace,
                          size_t workspace_bytes, void* stream);

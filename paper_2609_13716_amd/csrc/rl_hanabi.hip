@@ -696,6 +696,10 @@ __global__ __launch_bounds__(HN_RUN_NT) void hn_run_kernel(HnParams p, PolicyArg
 // MLP waves go first at the memory pipe); one loop for the env and helper waves (1.05,
 // the game's registers spill around the copy); o_t copied straight from the gapped rows
 // (three LDS words per vector) or partly by the env wave (1.13).
+// Registers: 168 per wave at 12 waves.  The env wave (the last tile's operands of layer 3
+// preloaded beside the game) spills: 70 VGPRs (284 bytes a lane) in the standard game at 512, 42 at
+// 256, 56 and 24 in the 3 x 3 game; compiled alone the MLP and the helper role spill none.
+// It is one wave of 12 and the figures above include it; without the spills is not measured.
 template <class G, int H>
 struct HnFs {
   static constexpr int TPW = H / 128;                    // unit tiles per MLP wave
@@ -1191,8 +1195,10 @@ static hipError_t launch_hn_run_fs(const HnParams& p, const PolicyArgs& pol, int
 template <class G>
 static hipError_t launch_hn_run_g(const HnParams& p, const PolicyArgs& pol, int32_t* state, uint64_t t0,
                                   int n_steps, const TrajArgs& out, hipStream_t s) {
-  // 256- and 512-wide packed policies: role-split kernel, faster from 1 to 16384 games (0.98 against 1.53 ms at 4096);
-  // it holds weights in registers and LDS, so the widths are compile-time
+  // 256- and 512-wide packed policies: role-split kernel, faster from 1 to 16384 games (0.98 against 1.53 ms at 4096;
+  // a single step of one or two games 256-wide without observations is the exception: 16.4 and 16.6 against 15.0 and
+  // 15.7 us); it holds weights in registers and LDS, so the widths are compile-time.  Others stay on hn_run_kernel
+  // (4096 games x 40 steps: 128-wide 451 us, 192 552, 320 651; role-split 256 413, 512 493)
   if (pol.Wp[0] != nullptr && pol.H1 == pol.H2 && (pol.H1 == 256 || pol.H1 == 512))
     return pol.H1 == 512 ? launch_hn_run_fs<G, 512>(p, pol, state, t0, n_steps, out, s)
                          : launch_hn_run_fs<G, 256>(p, pol, state, t0, n_steps, out, s);

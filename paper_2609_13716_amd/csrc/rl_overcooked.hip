@@ -709,7 +709,8 @@ hipError_t launch_oc_run(const OcParams& p, const PolicyArgs& pol, int32_t* stat
     return te == 16 ? launch_oc_run_te<DT_F32, 16, false>(p, pol, state, t0, n_steps, out, lds, s)
                     : launch_oc_run_te<DT_F32, 8, false>(p, pol, state, t0, n_steps, out, lds, s);
   // 256-wide packed policies: role-split kernel (3.45 against 4.82 ms at 4096 kitchens); it holds layer 2 in
-  // registers, so the widths are compile-time
+  // registers, so the widths are compile-time.  Other widths stay on oc_run_kernel (4096 kitchens x 50 steps: 64-wide
+  // 376 us, 128 416, 192 606, 320 877, 512 1244; role-split 256 442)
   if (pol.Wp[0] != nullptr && pol.H1 == FS_H && pol.H2 == FS_H) {
     const hipError_t e = hipFuncSetAttribute((const void*)oc_run_fs_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                              (int)sizeof(OcFsLds));

@@ -929,6 +929,8 @@ static_assert(HF_LDS <= MAX_LDS_BYTES, "one workgroup per CU");
 // (8192 rows) takes about 78 us full or not; the three GEMMs and the output kernel
 // 14 us and 13 us per 1000 rows: 4096 rows measured the same, 6000 rows 79
 // against 104 us per step, 8192 rows 78 against 120, 16384 rows 160 against 225.
+// The copies are made by every call and pay from one step on (one step and the
+// last value, copies included: 4096 rows 208 -> 195 us, 8192 rows 302 -> 211).
 // (At these sizes the weights' copy also fits where the GEMM path keeps its
 // activations.)
 static bool s5_heads_fused(int R, int H, int F) {
